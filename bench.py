@@ -7,7 +7,7 @@ Particles are resident on the GPU before the timed region.
 
 Prints one JSON line: value = finest-level cell updates per second over the
 whole step (n^3 * (nu_pre + nu_post) * cycles / step time), the dominant
-kernel's roofline (finest colour pass, timed with HIP events on the stream
+kernel's roofline (finest red-black sweep, timed with HIP events on the stream
 the solver launches on) and the FP64 CPU oracle timed on a bounded sample.
 """
 from __future__ import annotations
@@ -25,12 +25,12 @@ sys.path.insert(0, ROOT)
 N_MESH, N_PART, BOX, SEED = 512, 256, 512.0, 6
 H0RC, A, OMEGA_M, TOL = 1.0, 1.0, 0.3089, 1e-8
 HBM_PEAK_GBS = 8000.0
-# algorithmic bytes of one finest colour pass per mesh cell (FP64): read both
-# colour halves (8 B), the colour's delta (4 B), write the colour (4 B)
-PASS_BYTES_PER_CELL = 16
+# algorithmic bytes of one finest sweep (both colour passes in one launch) per
+# mesh cell (FP64): read the field (8 B) and delta (8 B), write the field (8 B)
+SWEEP_BYTES_PER_CELL = 24
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pass_dgp_512_traffic.json")
 KERNEL_SOURCES = ["paper_2110_00566_amd/csrc/mg_device.h", "paper_2110_00566_amd/csrc/mg_kernels.h",
-                  "paper_2110_00566_amd/csrc/mg_tiled.h"]
+                  "paper_2110_00566_amd/csrc/mg_tiled.h", "paper_2110_00566_amd/csrc/mg_sweep.h"]
 
 
 def kernel_hash() -> str:
@@ -41,7 +41,7 @@ def kernel_hash() -> str:
 
 
 def measured_traffic():
-    """HBM bytes per pass launch from the committed rocprofv3 counter runs,
+    """HBM bytes per sweep launch from the committed rocprofv3 counter runs,
     if they were taken on the current kernel source."""
     try:
         t = json.load(open(TRAFFIC_FILE))
@@ -72,11 +72,12 @@ def vcycle_bytes(n: int, fused: bool = False) -> int:
     """Algorithmic HBM bytes of one FP64 V(1,1) cycle: per level 4 colour
     passes (16 B/cell), residual + restriction (18) and prolongation (18),
     plus the coarse FAS source (40 B per coarse cell).  fused: the bytes the
-    executed kernels must move, where levels >= 128^3 fuse the prolongation
-    with the first post-smoothing pass (22 B/cell instead of 18 + 16)."""
+    executed kernels must move, where levels >= 128^3 run both colours of a
+    sweep in one launch (24 B/cell instead of 32) and the prolongation with
+    the first post-smoothing sweep (26 instead of 18 + 32)."""
     total, m, lev = 0, n, 0
     while m > 4:
-        per = 88 if (fused and m >= 128) else 100
+        per = 68 if (fused and m >= 128) else 100
         total += per * m ** 3 + (40 * m ** 3 if lev else 0)
         m //= 2
         lev += 1
@@ -412,8 +413,8 @@ def main():
     updates = sum(N_MESH ** 3 * 2 * c for c in cycles)
     ms_step = 1e3 * dt / args.steps
     solve_ms = 1e3 * float(np.mean([s.seconds for s in stats]))
-    pass_ms = prof.pass_ms_avg
-    achieved = PASS_BYTES_PER_CELL * N_MESH ** 3 / (pass_ms * 1e-3) / 1e9
+    sweep_ms = 2.0 * prof.pass_ms_avg   # a sweep counts as two colour passes
+    achieved = SWEEP_BYTES_PER_CELL * N_MESH ** 3 / (sweep_ms * 1e-3) / 1e9
     traffic = measured_traffic()
     out = {
         "metric": "cell-updates/s and time-to-residual 1e-8 per V-cycle at 512^3; % HBM peak",
@@ -438,11 +439,11 @@ def main():
                                for l in range(mg.LEVELS) if prof.level_ms[l] > 0],
         "profiled_step": {"time_to_tol_ms": 1e3 * prof.seconds, "pass_count": prof.pass_count},
         "ms_per_vcycle": solve_ms / float(np.mean(cycles)),
-        "roofline": {"bound": "hbm", "kernel": "k_pass_tiled<OP_DGP, double> (finest colour pass)",
+        "roofline": {"bound": "hbm", "kernel": "k_sweep_tiled<OP_DGP, double> (finest sweep)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic, "pass_ms_avg": pass_ms,
-                     "algorithmic_bytes_per_launch": PASS_BYTES_PER_CELL * N_MESH ** 3},
+                     "traffic": traffic, "sweep_ms_avg": sweep_ms,
+                     "algorithmic_bytes_per_launch": SWEEP_BYTES_PER_CELL * N_MESH ** 3},
     }
     # the same step with the two mixed-precision solves, to the same FP64
     # tolerance: "mixed" (MG_MIXED: FP32 cycles to the FP32 floor, then FP64

@@ -97,7 +97,7 @@ typedef struct {
                          comparator are FP64 */
     int cycle;        /* mg_cycle: MG_CYCLE_V (default), MG_CYCLE_F or MG_CYCLE_W;
                          mg_solve_adjoint accepts MG_CYCLE_V only */
-    int profile;      /* 1: time every finest-level colour pass with HIP events
+    int profile;      /* 1: time the finest-level smoothing with HIP events
                          on the caller's stream (stats.pass_ms_avg) */
     int delta_fp32;   /* 0: the solves' delta is FP64 (double *); 1: FP32 (float *),
                          any precision (it is widened or kept as the levels store
@@ -134,7 +134,9 @@ typedef struct {
     long long cell_updates;     /* n^3 * (nu_pre + nu_post) * cycles */
     long long n_clamped;        /* clamped discriminants (nDGP) */
     double seconds;             /* host wall clock of the call */
-    double pass_ms_avg;         /* mean finest colour-pass duration (profile=1) */
+    double pass_ms_avg;         /* mean finest colour-pass duration (profile=1); a sweep that
+                                   runs both colours in one launch (n >= 128) counts as two
+                                   passes of half its duration */
     int pass_count;             /* number of timed finest colour passes */
     int cycles_fp32;            /* MG_MIXED, MG_FP32: cycles in FP32 storage (included in cycles) */
     double eps_fp32;            /* MG_FP32: residual at the end of the FP32 cycles; MG_MIXED:

@@ -23,6 +23,7 @@
 #include "mg_adj_tiled.h"
 #include "mg_adjoint.h"
 #include "mg_dc.h"
+#include "mg_sweep.h"
 
 using namespace mgk;
 
@@ -108,6 +109,7 @@ struct Ctx {
     bool no_sync = false;
     std::vector<hipEvent_t> ev;
     int ev_used = 0;
+    int ev_passes = 0;   // colour passes between the recorded event pairs
     double pass_ms = 0.0;
     int pass_count = 0;
     // per-level timing (profile): events bracketing each level's segments
@@ -283,20 +285,40 @@ bool tiled_level(int n) { return n >= 128; }
 // The tiled kernels implement the closed-form update only.
 constexpr bool tiled_op(int OP) { return OP != OP_ADJ; }
 
-// z-planes per block: the deepest chunk (4 .. kzmax planes) that still gives
-// a launch at least 4096 blocks.  Deeper chunks re-read fewer z-halo planes;
-// at 1024^3 (128 planes, 8192 blocks per pass) the V-cycle is 1% faster than
-// with 64.  Kernels whose chunks count coarse planes (two fine planes each)
-// keep at most 64: the 1024^3 residual + restriction took 4.43 ms with 128
-// (4096 blocks) against 4.31 ms with 64.
-TileGeom tile_geom(int n, int planes, int kzmax = 128) {
+// z-planes per block: the deepest chunk (2 .. kzmax planes) that still gives
+// a launch at least 2048 blocks.  Deeper chunks re-read fewer z-halo planes;
+// fewer blocks leave a level of 128^3 latency-bound (its residual +
+// restriction took 24 us with 256 blocks, 18 us with 512, its coarse source
+// 22 and 18.6 us with 512 and 1024).  512^3: 4096, 2048 and 1024 blocks give
+// 555, 560 and 571 us for the residual + restriction, 123, 117 and 118 us for
+// the 256^3 coarse source.  Kernels whose chunks count coarse planes (two fine
+// planes each) keep at most 64: the 1024^3 residual + restriction took 4.43 ms
+// with 128 against 4.31 ms with 64.  The adjoint kernels, which stage four planes
+// before the first result, keep at least 4 (128^3 gradient 8.6 ms, 8.9 with 2).
+TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2) {
     TileGeom G;
     G.ntx = (n / 2) / TX;
     G.nty = n / TY;
     const long per = (long)G.ntx * G.nty;
     int kz = kzmax;
-    while (kz > 4 && (long)planes * per / kz < 4096) kz >>= 1;
+    while (kz > kzmin && (long)planes * per / kz < 2048) kz >>= 1;
     while (planes % kz) kz >>= 1;
+    G.kz = kz;
+    return G;
+}
+
+// z-planes per block of the sweep kernel, whose chunks re-read four planes and
+// recompute two: the deepest chunk (4 .. 128 planes) that gives the launch two
+// blocks per CU, 512, which is also what is resident.  512^3 solve with at
+// most 32, 64 and 128 planes: 33.9, 33.4 and 32.9 ms; 256^3 with 512 blocks
+// (32 planes) 5.89 ms, with 1024 6.06 ms, with 256 6.38 ms.
+TileGeom sweep_geom(int n) {
+    TileGeom G;
+    G.ntx = (n / 2) / TX;
+    G.nty = n / TY;
+    const long per = (long)G.ntx * G.nty;
+    int kz = 128;
+    while (kz > 4 && n / kz * per < 512) kz >>= 1;
     G.kz = kz;
     return G;
 }
@@ -307,16 +329,17 @@ unsigned tile_blocks(const TileGeom &G, int planes) {
 
 constexpr int fwd_op(int OP) { return OP == OP_ADJ ? OP_DGP : OP; }
 
-template <int OP, typename R>
-void launch_pass(const Mod &M, const LvlT<R> &L, const Coefs &Cf, int c, R *out, const double *fptr,
-                 double fs, unsigned long long *clamp, hipStream_t st) {
-    if (tiled_op(OP) && tiled_level(L.n)) {
+// One colour pass on its own (mg_op_colour_pass; the solves run both colours
+// of a tiled level in one k_sweep_tiled launch).
+template <int OP>
+void launch_pass(const Mod &M, const Lvl &L, const Coefs &Cf, int c, double *out,
+                 hipStream_t st) {
+    if (tiled_level(L.n)) {
         const TileGeom G = tile_geom(L.n, L.n);
-        k_pass_tiled<fwd_op(OP), R><<<tile_blocks(G, L.n), TPB, 0, st>>>(M, L, c, out, fptr, fs,
-                                                                         clamp, G);
+        k_pass_tiled<OP><<<tile_blocks(G, L.n), TPB, 0, st>>>(M, L, c, out, G);
     } else {
         const size_t half = (size_t)L.n * L.n * L.n / 2;
-        k_pass<OP, R><<<nblocks(half), TPB, 0, st>>>(M, L, Cf, c, out, fptr, fs, clamp);
+        k_pass<OP, double><<<nblocks(half), TPB, 0, st>>>(M, L, Cf, c, out, nullptr, 0.0, nullptr);
     }
 }
 
@@ -390,7 +413,7 @@ template <int MODE, bool REDUCE>
 unsigned launch_adj_tiled(int model, const AdjLevel &A, int c, double *out, double *out2,
                           const double *fptr, double fscale, double *ru0, double *ru1,
                           double *rd0, double *rd1, double *partials, hipStream_t st) {
-    const TileGeom G = tile_geom(A.n, A.n, 64);
+    const TileGeom G = tile_geom(A.n, A.n, 64, 4);
     const unsigned nb = tile_blocks(G, A.n);
     switch (model) {
         case MODEL_KMO:
@@ -536,23 +559,60 @@ struct Solver {
                 if (timed) {
                     (void)hipEventRecord(C.ev[C.ev_used + 1], C.st);
                     C.ev_used += 2;
+                    ++C.ev_passes;
                 }
                 std::swap(H.u[c], H.spare);
                 return;
             }
         }
-        launch_pass<OP, R>(C.M, view(H, l > 0 || OP == OP_ADJ), coefs(H), c, H.spare, fptr, fs,
-                           C.clamp, C.st);
+        k_pass<OP, R><<<nblocks(H.half), TPB, 0, C.st>>>(C.M, view(H, l > 0 || OP == OP_ADJ),
+                                                         coefs(H), c, H.spare, fptr, fs, C.clamp);
         if (timed) {
             (void)hipEventRecord(C.ev[C.ev_used + 1], C.st);
             C.ev_used += 2;
+            ++C.ev_passes;
         }
         std::swap(H.u[c], H.spare);
     }
 
+    // Both colour passes of a sweep in one launch (levels >= 128^3).
+    bool fused_sweep(int l) const {
+        return tiled_op(OP) && Hh.lv[l].spare2 && tiled_level(Hh.lv[l].n);
+    }
+    // PROLONG: preceded by the prolongation of level l + 1's correction.
+    template <bool PROLONG>
+    void launch_sweep(int l) {
+        HLevel<R> &H = Hh.lv[l];
+        SweepCoarse<R> K{};
+        if (PROLONG) {
+            const HLevel<R> &Hc = Hh.lv[l + 1];
+            K = {Hc.u[0], Hc.u[1], Hc.ru[0], Hc.ru[1]};
+        }
+        const TileGeom G = sweep_geom(H.n);
+        const unsigned nb = tile_blocks(G, H.n);
+        if (l > 0)
+            k_sweep_tiled<fwd_op(OP), R, true, PROLONG><<<nb, SNT, 0, C.st>>>(
+                C.M, view(H, true), H.spare, H.spare2, K, nullptr, 0.0, C.clamp, G);
+        else
+            k_sweep_tiled<fwd_op(OP), R, false, PROLONG><<<nb, SNT, 0, C.st>>>(
+                C.M, view(H, false), H.spare, H.spare2, K, C.scal + S_MU, 1.0, C.clamp, G);
+        std::swap(H.u[0], H.spare);
+        std::swap(H.u[1], H.spare2);
+    }
     void sweep(int l) {
-        pass(l, 0);
-        pass(l, 1);
+        if (!fused_sweep(l)) {
+            pass(l, 0);
+            pass(l, 1);
+            return;
+        }
+        const bool timed = C.profile && l == 0 && C.ev_used + 2 <= (int)C.ev.size();
+        if (timed) (void)hipEventRecord(C.ev[C.ev_used], C.st);
+        launch_sweep<false>(l);
+        if (timed) {
+            (void)hipEventRecord(C.ev[C.ev_used + 1], C.st);
+            C.ev_used += 2;
+            C.ev_passes += 2;
+        }
     }
 
     // residual (+ statistics on the finest level) and restriction into l+1
@@ -652,20 +712,6 @@ struct Solver {
         launch_prolong<R>(H.u[0], H.u[1], H.logn, Hc.u[0], Hc.u[1], Hc.ru[0], Hc.ru[1], C.st);
     }
 
-    // prolongation fused with the colour-0 pass of the first post-sweep
-    bool fused_prolong(int l) const {
-        return tiled_op(OP) && C.nu2 >= 1 && Hh.lv[l].spare2 && tiled_level(Hh.lv[l].n);
-    }
-    void prolong_pass0(int l) {
-        HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
-        const TileGeom G = tile_geom(H.n, H.n);
-        k_prolong_pass_tiled<fwd_op(OP), R><<<tile_blocks(G, H.n), TPB, 0, C.st>>>(
-            C.M, view(H, l > 0), H.spare, H.spare2, Hc.u[0], Hc.u[1], Hc.ru[0], Hc.ru[1],
-            l == 0 ? C.scal + S_MU : nullptr, 1.0, C.clamp, G);
-        std::swap(H.u[0], H.spare);
-        std::swap(H.u[1], H.spare2);
-    }
-
     template <int NL>
     void launch_tail(const TailArgs<R> &A, size_t lds) {
         // once per instantiation and process (thread-safe); a failure stays
@@ -753,9 +799,8 @@ struct Solver {
             cycle(l + 1, 0);
         }
         const int e2 = mark();
-        if (fused_prolong(l)) {
-            prolong_pass0(l);
-            pass(l, 1);
+        if (C.nu2 >= 1 && fused_sweep(l)) {
+            launch_sweep<true>(l);   // the first post-sweep, prolongation included
             for (int s = 1; s < C.nu2; ++s) sweep(l);
         } else {
             prolong(l);
@@ -790,9 +835,10 @@ struct Solver {
                 float ms = 0.f;
                 HIPCHK(hipEventElapsedTime(&ms, C.ev[q], C.ev[q + 1]));
                 C.pass_ms += ms;
-                ++C.pass_count;
             }
+            C.pass_count += C.ev_passes;
             C.ev_used = 0;
+            C.ev_passes = 0;
             for (const auto &g : C.segs) {
                 float ms = 0.f;
                 HIPCHK(hipEventElapsedTime(&ms, C.lev_ev[g.e0], C.lev_ev[g.e1]));
@@ -1312,8 +1358,7 @@ void op_residual_launch(const Mod &M, OpWs &W, hipStream_t s, bool with_f) {
 template <int OP>
 void op_pass_launch(const Mod &M, OpWs &W, int colour, hipStream_t s) {
     HLevel<double> &H = W.H;
-    launch_pass<OP, double>(M, view(H, true), coefs(H), colour, colour ? W.out[1] : W.out[0],
-                            nullptr, 0.0, nullptr, s);
+    launch_pass<OP>(M, view(H, true), coefs(H), colour, colour ? W.out[1] : W.out[0], s);
 }
 
 void pack_f(OpWs &W, const double *f, double fs, hipStream_t s) {

@@ -58,6 +58,20 @@ struct NbT {
 };
 using Nb = NbT<double>;
 
+// The combinations of a neighbourhood that the operators use: per axis the
+// sum a = (+) + (-) and the difference e = (+) - (-) of the face neighbours,
+// and the cross differences.
+template <typename T>
+struct CombT {
+    T ax, ay, az, ex, ey, ez, nxy, nxz, nyz;
+    __device__ __forceinline__ T faces() const { return ax + ay + az; }
+};
+template <typename T>
+__device__ __forceinline__ CombT<T> comb(const NbT<T> &s) {
+    return {s.xp + s.xm, s.yp + s.ym, s.zp + s.zm, s.xp - s.xm, s.yp - s.ym,
+            s.zp - s.zm, s.nxy,       s.nxz,       s.nyz};
+}
+
 // Neighbourhood of the cell of colour c at packed (m, j, k).  A holds colour
 // c (edge neighbours), B colour 1-c (face neighbours).
 template <typename T, typename R>
@@ -102,9 +116,9 @@ __device__ __forceinline__ NbT<T> load_nb(const R *__restrict__ A, const R *__re
 // 2 Sigma / (alpha + sign(alpha) sqrt(D)).  D < 0 is clamped to 0 (K = -3 alpha/4).
 // Sigma / alpha of the nDGP operator at one cell (no centre dependence).
 template <typename T, typename L_>
-__device__ __forceinline__ T dgp_sigma_over_alpha(const Mod &M, const L_ &L, const NbT<T> &s,
+__device__ __forceinline__ T dgp_sigma_over_alpha(const Mod &M, const L_ &L, const CombT<T> &s,
                                                   T delta) {
-    const T ax = s.xp + s.xm, ay = s.yp + s.ym, az = s.zp + s.zm;
+    const T ax = s.ax, ay = s.ay, az = s.az;
     const T dxy = ax - ay, dxz = ax - az, dyz = ay - az;
     const T t3 = dxy * dxy + dxz * dxz + dyz * dyz;
     const T t8 = s.nxy * s.nxy + s.nxz * s.nxz + s.nyz * s.nyz;
@@ -112,53 +126,85 @@ __device__ __forceinline__ T dgp_sigma_over_alpha(const Mod &M, const L_ &L, con
     return (T)(sig / M.alpha);
 }
 
-template <int MODEL, typename T, typename L_>
-__device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const NbT<T> &s, T delta,
-                                        unsigned long long *clamp) {
+template <typename T, typename L_>
+__device__ __forceinline__ T dgp_sigma_over_alpha(const Mod &M, const L_ &L, const NbT<T> &s,
+                                                  T delta) {
+    return dgp_sigma_over_alpha<T>(M, L, comb(s), delta);
+}
+
+// Square root of a positive x that needs no scaling (x > 2^-767): the Newton
+// iterations on the hardware's reciprocal root estimate that sqrt() runs,
+// with its result, without the scaling and special-case instructions around
+// them.  NaN stays NaN; infinity gives NaN.
+__device__ __forceinline__ double sqrt_normal(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return fma(fma(-g, g, x), h, g);
+}
+
+// clamp: count of clamped discriminants, a device counter (added to with an
+// atomic; may be null) or the calling thread's own.
+__device__ __forceinline__ void count_clamp(unsigned long long *c) {
+    if (c) atomicAdd(c, 1ull);
+}
+__device__ __forceinline__ void count_clamp(unsigned *c) { ++*c; }
+
+template <int MODEL, typename T, typename L_, typename Clamp>
+__device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T> &s, T delta,
+                                        Clamp *clamp) {
     if (MODEL == MODEL_POISSON) return (T)M.s * delta;
-    const T ax = s.xp + s.xm, ay = s.yp + s.ym, az = s.zp + s.zm;
+    const T ax = s.ax, ay = s.ay, az = s.az;
     if (MODEL == MODEL_DGP) {
         const T dxy = ax - ay, dxz = ax - az, dyz = ay - az;
-        const T t3 = dxy * dxy + dxz * dxz + dyz * dyz;
-        const T t8 = s.nxy * s.nxy + s.nxz * s.nxz + s.nyz * s.nyz;
         if constexpr (sizeof(T) == 4) {
             // FP32 storage: the whole term in FP32, the root in the
             // cancellation-free form 2 Sigma / (alpha + sign(alpha) sqrt(D))
             // (equal to the printed one; accurate relative to K when
             // Sigma << alpha^2).  A clamped D gives -3 alpha / 4 as above.
-            const float sig = t3 * (float)L.c3h4 + t8 * (float)L.c8h4 + (float)M.s * delta;
-            const float disc = (float)(M.alpha * M.alpha) + (8.0f / 3.0f) * sig;
+            // The products are fused explicitly, so that every kernel rounds
+            // the term alike.
+            const float u3 = fmaf(dyz, dyz, fmaf(dxy, dxy, dxz * dxz));
+            const float u8 = fmaf(s.nyz, s.nyz, fmaf(s.nxy, s.nxy, s.nxz * s.nxz));
+            const float sig = fmaf((float)M.s, delta,
+                                   fmaf(u3, (float)L.c3h4, u8 * (float)L.c8h4));
+            const float disc = fmaf(8.0f / 3.0f, sig, (float)(M.alpha * M.alpha));
             if (disc < 0.0f) {
-                if (clamp) atomicAdd(clamp, 1ull);
+                count_clamp(clamp);
                 return (T)(-0.75 * M.alpha);
             }
-            return 2.0f * sig / ((float)M.alpha + (float)M.sgn * sqrtf(disc));
+            return 2.0f * sig / fmaf((float)M.sgn, sqrtf(disc), (float)M.alpha);
         }
+        const T t3 = dxy * dxy + dxz * dxz + dyz * dyz;
+        const T t8 = s.nxy * s.nxy + s.nxz * s.nxz + s.nyz * s.nyz;
         const double sig = (double)t3 * L.c3h4 + (double)t8 * L.c8h4 + M.s * (double)delta;
         double disc = M.alpha * M.alpha + (8.0 / 3.0) * sig;
-        if (disc < 0.0) {
-            disc = 0.0;
-            if (clamp) atomicAdd(clamp, 1ull);
-        }
-        return (T)(0.75 * (M.sgn * sqrt(disc) - M.alpha));
+        if (disc < 0.0) count_clamp(clamp);
+        disc = disc < 1e-280 ? 1e-280 : disc;   // root 1e-140: nothing beside alpha
+        return (T)(0.75 * (M.sgn * sqrt_normal(disc) - M.alpha));
     }
     // Kmouflage split form eq:kmf_eqn_codeunit_final: with e = 2h grad phi,
     //   g = |e|^2/(4h^2),  Q = hat(H)_ij G_i G_j
     //     = [e_x^2 (2A_x-A_y-A_z) + ...]/(12 h^4) + (N_xy e_x e_y + ...)/(8 h^4),
     //   K = (src delta + b2 g^(n-2) Q) / (c~ (c0 + a1 g^(n-1))).
-    const T ex = s.xp - s.xm, ey = s.yp - s.ym, ez = s.zp - s.zm;
+    const T ex = s.ex, ey = s.ey, ez = s.ez;
     if constexpr (sizeof(T) == 4) {
         // FP32 storage: the whole term in FP32 (its relative error stays far
-        // below that of the FP32-stored field)
-        const float g = (ex * ex + ey * ey + ez * ez) * (float)L.c4h2;
-        const float q = (ex * ex * (2 * ax - ay - az) + ey * ey * (2 * ay - ax - az)
-                         + ez * ez * (2 * az - ax - ay)) * (float)L.c12h4
-                      + (s.nxy * ex * ey + s.nxz * ex * ez + s.nyz * ey * ez) * (float)L.c8h4;
+        // below that of the FP32-stored field), products fused explicitly
+        const float ey2 = ey * ey;
+        const float g = fmaf(ez, ez, fmaf(ex, ex, ey2)) * (float)L.c4h2;
+        const float tx = fmaf(2.0f, ax, -ay) - az, ty = fmaf(2.0f, ay, -ax) - az,
+                    tz = fmaf(2.0f, az, -ax) - ay;
+        const float q3 = fmaf(ez * ez, tz, fmaf(ex * ex, tx, ey2 * ty));
+        const float q8 = fmaf(ez, ey * s.nyz, fmaf(ey, ex * s.nxy, ez * (ex * s.nxz)));
+        const float q = fmaf(q3, (float)L.c12h4, q8 * (float)L.c8h4);
         float gn2 = 1.0f;
         for (int t = 0; t < M.nk - 2; ++t) gn2 *= g;
-        const float sig1 = (float)M.c0 + (float)M.a1 * gn2 * g;
-        const float sig2 = (float)M.b2 * gn2 * q;
-        return ((float)M.src * delta + sig2) / ((float)M.ctil * sig1);
+        const float sig1 = fmaf(g, gn2 * (float)M.a1, (float)M.c0);
+        return fmaf(delta, (float)M.src, q * (gn2 * (float)M.b2)) / ((float)M.ctil * sig1);
     }
     const double g = (double)(ex * ex + ey * ey + ez * ez) * L.c4h2;
     const double q = (double)(ex * ex * (2 * ax - ay - az) + ey * ey * (2 * ay - ax - az)
@@ -169,6 +215,12 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const NbT<T> 
     const double sig1 = M.c0 + M.a1 * gn2 * g;
     const double sig2 = M.b2 * gn2 * q;
     return (T)((M.src * (double)delta + sig2) / (M.ctil * sig1));
+}
+
+template <int MODEL, typename T, typename L_, typename Clamp>
+__device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const NbT<T> &s, T delta,
+                                        Clamp *clamp) {
+    return model_term<MODEL, T>(M, L, comb(s), delta, clamp);
 }
 
 // Correction form of the nDGP model term, used by the defect-correction

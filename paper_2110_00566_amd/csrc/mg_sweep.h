@@ -1,0 +1,441 @@
+// One red-black sweep (colour-0 pass, then colour-1 pass) of a level in a
+// single launch, for levels with at least 128 cells per side.
+//
+// Two launches of the colour pass read both colours of the field twice:
+// 2 x 16 B per cell in FP64.  Here a block marches through its z-chunk with
+// the colour-1 update two planes behind the colour-0 update, so the field
+// and delta are read once and written once: 24 B per cell.
+//
+// A block owns a tile of 64 packed columns x 8 rows, one wave per row.
+// Colour-1 cells at the tile's edge need new colour-0 values outside it, so
+// the colour-0 update also covers the rows above and below the tile (waves 0
+// and 1) and the cell beside each row's end that the colour-1 cells reach
+// (lanes 0..19 of wave 2); 12 rows x 66 columns of the old field are staged
+// per plane.
+//
+// A plane is read from LDS once per column.  What a cell needs of the planes
+// above and below is its own column of the opposite colour and the x and y
+// differences of its own colour there (the xz and yz cross terms), and since
+// the packed parity of a column alternates from plane to plane, the
+// differences that the cells of planes k - 1 and k + 1 need of plane k are the
+// same ones.  A thread therefore carries them in registers (ColRead) instead
+// of reading three staged planes per cell, which also keeps the ring of
+// staged planes short enough for two blocks of 512 threads per CU.
+//
+// Step kp (after one barrier) reads plane kp, finishes the colour-0 cells of
+// plane kp - 1 and the colour-1 cells of plane kp - 3, writes the staged
+// values of plane kp + 1 and starts the loads of plane kp + 2.
+#pragma once
+#include <type_traits>
+#include "mg_tiled.h"
+
+namespace mgk {
+
+constexpr int SNT = 512;              // threads: a wave per tile row
+constexpr int SROWS = TY + 4;         // staged rows -2 .. TY + 1
+constexpr int SPLANE = SROWS * TXH;   // 792 values per staged plane
+constexpr int SSLOT = SPLANE + 2;     // one value before (vector alignment) and one after
+static_assert(SNT == 64 * TY, "one wave per tile row");
+
+// Coarse values around a tile for the prolongation: columns m0 - 2 .. m0 + 65
+// (a packed column holds the two children of one coarse column) and coarse
+// rows j0/2 - 2 .. j0/2 + 5, one per wave.
+constexpr int SCW = TX + 4, SCH = SROWS / 2 + 2, SCPLANE = SCW * SCH;
+static_assert(SCH * 64 == SNT, "one wave per coarse row");
+
+// Staging of a plane of both colours: 16-byte vectors of the 64 interior
+// columns by the last NV threads, the two halo columns by the first 24.
+template <typename R>
+struct SweepStage {
+    static constexpr int VW = 16 / sizeof(R);       // values per vector
+    static constexpr int VPR = TX / VW;             // vectors per row
+    static constexpr int NV = SROWS * VPR;          // 384 (FP64), 192 (FP32)
+    static constexpr int V0 = SNT - NV;             // first vector thread
+    static_assert(V0 >= 64 && V0 % 64 == 0 && 2 * SROWS <= 64, "staging split");
+    typedef R Vec __attribute__((ext_vector_type(VW)));
+    unsigned g;   // byte offset inside a plane
+    int l;        // value offset inside a plane view
+    Vec a, b;
+    __device__ __forceinline__ void init(int tid, int j0, int m0, int logn, int lognh) {
+        const unsigned jm = (1u << logn) - 1, mm = (1u << lognh) - 1;
+        int r, q;
+        unsigned m;
+        if (tid >= V0) {
+            r = (tid - V0) / VPR;
+            const int i = (tid - V0) % VPR;
+            q = 1 + VW * i;
+            m = (unsigned)(m0 + VW * i);
+        } else {
+            const int side = tid & 1;
+            r = tid < 2 * SROWS ? tid >> 1 : 0;
+            q = side ? TXH - 1 : 0;
+            m = (unsigned)(side ? m0 + TX : m0 - 1) & mm;
+        }
+        g = ((((unsigned)(j0 - 2 + r) & jm) << lognh) + m) * (unsigned)sizeof(R);
+        l = r * TXH + q;
+    }
+    __device__ __forceinline__ void fetch(const R *A, const R *B, size_t pl, int w, int lane) {
+        const char *pa = reinterpret_cast<const char *>(A) + pl + g;
+        const char *pb = reinterpret_cast<const char *>(B) + pl + g;
+        if (w >= V0 / 64) {
+            a = *reinterpret_cast<const Vec *>(pa);
+            b = *reinterpret_cast<const Vec *>(pb);
+        } else if (w == 0 && lane < 2 * SROWS) {
+            a[0] = *reinterpret_cast<const R *>(pa);
+            b[0] = *reinterpret_cast<const R *>(pb);
+        }
+    }
+    // Add the prolonged coarse correction to the fetched values of a plane k
+    // (odd: k & 1).  eo, en: the coarse correction in the plane's own coarse
+    // plane and in its neighbour on the plane's side; ec, ed: offsets there of
+    // the own coarse row and of its neighbour on the row's side (ed > ec: the
+    // row is odd).  The 27/9/3/1 weights factor into 9, 3, 3, 1 in the plane
+    // and 3, 1 between the planes; FP32 rounds in this order in every kernel.
+    template <int N>
+    __device__ __forceinline__ void correct(const R *eo, const R *en, int ec, int ed, bool odd) {
+        const R w9 = (R)(9.0 / 16.0), w3 = (R)(3.0 / 16.0), w1 = (R)(1.0 / 16.0);
+        const bool p0 = (ed > ec) != odd;   // x parity of the colour-0 values
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            R x[2][2];   // own and neighbouring plane, x parity
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                const R *e = z ? en : eo;
+                const R c = w9 * e[ec + i], d = e[ed + i];
+                x[z][0] = fma(w1, e[ed + i - 1], fma(w3, d, fma(w3, e[ec + i - 1], c)));
+                x[z][1] = fma(w1, e[ed + i + 1], fma(w3, d, fma(w3, e[ec + i + 1], c)));
+            }
+            R v[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                v[q] = odd ? fma((R)0.75, x[0][q], (R)0.25 * x[1][q])
+                           : fma((R)0.25, x[1][q], (R)0.75 * x[0][q]);
+            a[i] += p0 ? v[1] : v[0];
+            b[i] += p0 ? v[0] : v[1];
+        }
+    }
+    __device__ __forceinline__ void correct(const R *eo, const R *en, int ec, int ed, bool odd,
+                                            int w, int lane) {
+        if (w >= V0 / 64)
+            correct<VW>(eo, en, ec, ed, odd);
+        else if (w == 0 && lane < 2 * SROWS)
+            correct<1>(eo, en, ec, ed, odd);
+    }
+    // sa, sb: the slots' plane views (slot base + 1)
+    __device__ __forceinline__ void store(R *sa, R *sb, int w, int lane) const {
+        if (w >= V0 / 64) {
+            if constexpr (sizeof(R) == 8) {
+                *reinterpret_cast<Vec *>(sa + l) = a;
+                *reinterpret_cast<Vec *>(sb + l) = b;
+            } else {   // rows start 8 bytes off a 16-byte boundary in places
+                *reinterpret_cast<float2 *>(sa + l) = make_float2(a[0], a[1]);
+                *reinterpret_cast<float2 *>(sa + l + 2) = make_float2(a[2], a[3]);
+                *reinterpret_cast<float2 *>(sb + l) = make_float2(b[0], b[1]);
+                *reinterpret_cast<float2 *>(sb + l + 2) = make_float2(b[2], b[3]);
+            }
+        } else if (w == 0 && lane < 2 * SROWS) {
+            sa[l] = a[0];
+            sb[l] = b[0];
+        }
+    }
+};
+
+// What a column takes from one plane: the x and y neighbours of its own
+// colour (for the cross terms of the cells one plane above and below), its
+// own column of the opposite colour, and the in-plane combinations of its
+// own cell there.  FP32 keeps the four neighbours themselves, so that the
+// cross terms are summed in the order of the colour pass and the results are
+// its results to the bit; FP64 keeps their differences.
+template <typename R>
+struct ZEdge {
+    R xp, xm, yp, ym;
+};
+template <>
+struct ZEdge<double> {
+    double x, y;
+};
+__device__ __forceinline__ void zedge(ZEdge<float> &e, float xp, float xm, float yp, float ym) {
+    e = {xp, xm, yp, ym};
+}
+__device__ __forceinline__ void zedge(ZEdge<double> &e, double xp, double xm, double yp,
+                                      double ym) {
+    e = {xp - xm, yp - ym};
+}
+__device__ __forceinline__ void zcross(const ZEdge<float> &p, const ZEdge<float> &m, float &nxz,
+                                       float &nyz) {
+    nxz = (p.xp + m.xm) - (m.xp + p.xm);
+    nyz = (p.yp + m.ym) - (m.yp + p.ym);
+}
+__device__ __forceinline__ void zcross(const ZEdge<double> &p, const ZEdge<double> &m,
+                                       double &nxz, double &nyz) {
+    nxz = p.x - m.x;
+    nyz = p.y - m.y;
+}
+
+template <typename R>
+struct ZPart {   // of a plane above or below the cell
+    ZEdge<R> e;
+    R b;
+    // A: own colour, B: opposite colour (plane views); o: the column's offset,
+    // ox: of the right one of its two x neighbours in A, o or o + 1
+    __device__ __forceinline__ void read(const R *A, const R *B, int o, int ox) {
+        zedge(e, A[ox], A[ox - 1], A[o + TXH], A[o - TXH]);
+        b = B[o];
+    }
+};
+template <typename R>
+struct XyPart {   // of the cell's own plane
+    R ax, ay, ex, ey, nxy, u;
+    __device__ __forceinline__ void read(const R *A, const R *B, int o, int ox) {
+        const R xp = B[ox], xm = B[ox - 1], yp = B[o + TXH], ym = B[o - TXH];
+        ax = xp + xm;
+        ay = yp + ym;
+        ex = xp - xm;
+        ey = yp - ym;
+        nxy = (A[ox + TXH] + A[ox - TXH - 1]) - (A[ox - TXH] + A[ox + TXH - 1]);
+        u = A[o];
+    }
+};
+template <typename R>
+__device__ __forceinline__ CombT<R> col_comb(const ZPart<R> &above, const XyPart<R> &c,
+                                             const ZPart<R> &below) {
+    CombT<R> s;
+    s.ax = c.ax;
+    s.ay = c.ay;
+    s.az = above.b + below.b;
+    s.ex = c.ex;
+    s.ey = c.ey;
+    s.ez = above.b - below.b;
+    s.nxy = c.nxy;
+    zcross(above.e, below.e, s.nxz, s.nyz);
+    return s;
+}
+
+// coarse level of a prolongation: the correction is u - Ru
+template <typename R>
+struct SweepCoarse {
+    const R *u0, *u1, *r0, *r1;
+};
+
+// PROLONG: the sweep starts from the prolonged field (first post-smoothing
+// sweep): the coarse correction is added while the planes are staged.
+template <int OP, typename R, bool HASF, bool PROLONG>
+__global__ __launch_bounds__(SNT)
+__attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *__restrict__ out0,
+                                                           R *__restrict__ out1,
+                                                           SweepCoarse<R> K, const double *fptr,
+                                                           double fscale,
+                                                           unsigned long long *clamp,
+                                                           TileGeom G) {
+    // ring of staged planes: slot k & 3 holds plane k of colours 0 and 1
+    __shared__ __align__(16) R sS[4][2][SSLOT];
+    __shared__ R sC[2][TPLANE];   // new colour-0 values, rows -1 .. TY
+    // ring of coarse planes (the correction): slot Z & 3
+    __shared__ R sE[PROLONG ? 4 : 1][PROLONG ? SCPLANE : 1];
+    const size_t blk = xcd_block(blockIdx.x, gridDim.x);
+    const int bx = (int)(blk % G.ntx);
+    const int by = (int)((blk / G.ntx) % G.nty);
+    const int bz = (int)(blk / ((size_t)G.ntx * G.nty));
+    const int m0 = bx * TX, j0 = by * TY, k0 = bz * G.kz, k1 = k0 + G.kz;   // kz is even
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const R fs = (R)(fptr ? fscale * (*fptr) : 0.0);
+    SweepStage<R> S;
+    S.init(tid, j0, m0, L.logn, L.lognh);
+    auto fetch = [&](int k) { S.fetch(L.u0, L.u1, plane_off<R>(k, L.logn, L.lognh), w, lane); };
+
+    // coarse correction: a wave loads the first 64 columns of its coarse row,
+    // and wave 1, which stages no fine values, the last 4 of all rows (through
+    // its staging registers).  Offsets carry the colour of (X + Y) in bit 0.
+    R cu = 0, cr = 0;
+    unsigned cg = 0;
+    int ec = 0, ed = 0;
+    const int lnc = L.logn - 1, ncm = (1 << lnc) - 1;
+    if constexpr (PROLONG) {
+        auto coff_of = [&](int row, int col) {
+            const int X = (m0 - 2 + col) & ncm, Y = ((j0 >> 1) - 2 + row) & ncm;
+            return ((((unsigned)Y << (lnc - 1)) + (unsigned)(X >> 1)) * (unsigned)sizeof(R)) |
+                   (unsigned)((X + Y) & 1);
+        };
+        cg = coff_of(w, lane);
+        const int r = S.l / TXH, q = S.l - r * TXH;
+        ec = ((r >> 1) + 1) * SCW + q + 1;
+        ed = ec + ((r & 1) ? SCW : -SCW);
+        if (w == 1) {
+            S.g = coff_of((lane >> 2) & 7, TX + (lane & 3));
+            S.l = ((lane >> 2) & 7) * SCW + TX + (lane & 3);
+        }
+    }
+    auto cload = [&](unsigned g, int Z, R &u, R &r) {
+        const size_t off = (((size_t)(Z & ncm) << (2 * lnc - 1)) * sizeof(R)) + (g & ~1u);
+        const bool odd = (g ^ (unsigned)Z) & 1u;
+        u = *reinterpret_cast<const R *>(reinterpret_cast<const char *>(odd ? K.u1 : K.u0) + off);
+        r = *reinterpret_cast<const R *>(reinterpret_cast<const char *>(odd ? K.r1 : K.r0) + off);
+    };
+    auto cfetch = [&](int Z) {
+        if constexpr (PROLONG) {
+            cload(cg, Z, cu, cr);
+            if (w == 1 && lane < 4 * SCH) {
+                R u, r;
+                cload(S.g, Z, u, r);
+                S.a[0] = u;
+                S.b[0] = r;
+            }
+        }
+    };
+    auto cstore = [&](int Z) {
+        if constexpr (PROLONG) {
+            R *E = sE[Z & 3];
+            E[w * SCW + lane] = cu - cr;
+            if (w == 1 && lane < 4 * SCH) E[S.l] = S.a[0] - S.b[0];
+        }
+    };
+    // the fetched plane k (par: k & 1) into its ring slot
+    auto stage = [&](int k, auto par) __attribute__((always_inline)) {
+        if constexpr (PROLONG) {
+            constexpr bool odd = decltype(par)::value;
+            const int Z = k >> 1;
+            S.correct(sE[Z & 3], sE[(odd ? Z + 1 : Z - 1) & 3], ec, ed, odd, w, lane);
+        }
+        S.store(sS[k & 3][0] + 1, sS[k & 3][1] + 1, w, lane);
+    };
+
+    // own column: row w, packed column lane
+    int o = (w + 2) * TXH + 1 + lane;
+    unsigned coff = cell_off<R>(j0 + w, m0 + lane, L.lognh);
+    // extra colour-0 column of waves 0..2
+    const int ye = w == 0 ? -1 : w == 1 ? TY : (lane >> 1) - 1;
+    const int qe = w < 2 ? 1 + lane : (lane & 1) ? TXH - 1 : 0;
+    const bool extra = w < 2 || (w == 2 && lane < 2 * TYH);
+    int oe = extra ? (ye + 2) * TXH + qe : o;
+    unsigned coffe =
+        cell_off<R>((j0 + ye) & (L.n - 1), (m0 - 1 + qe) & ((1 << L.lognh) - 1), L.lognh);
+
+    ZPart<R> P[2] = {}, Q[2] = {};   // colour 0 and colour 1: the last two planes
+    XyPart<R> q = {};                // colour 1: the last plane
+    R d0n = 0, dxn = 0, d1n = 0, f0n = 0, fxn = 0, f1n = 0;
+    unsigned nclamp = 0;
+    auto update = [&](const ZPart<R> &above, const XyPart<R> &c, const ZPart<R> &below, R delta,
+                      R f, bool count) {
+        const CombT<R> s = col_comb(above, c, below);
+        unsigned neg = 0;
+        const R nv = tiled_update<OP, R>(M, L, s, delta, s.faces(), c.u, f + fs, &neg);
+        if (count) nclamp += neg;
+        return nv;
+    };
+    // One step; PAR = kp & 1.  FULL: a step with all its parts (planes
+    // k0 + 3 .. k1 - 1), free of branches on kp.
+    auto step = [&](int kp, auto par, auto full) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par)::value;
+        constexpr bool FULL = decltype(full)::value;
+        // opaque copies: the addresses derived from them are formed again in
+        // every step instead of being kept in registers for the whole march
+        asm("" : "+v"(o), "+v"(oe), "+v"(coff), "+v"(coffe), "+v"(S.g), "+v"(S.l));
+        if constexpr (PROLONG) asm("" : "+v"(ec), "+v"(ed), "+v"(cg));
+        if (FULL || kp <= k1) stage(kp + 1, std::integral_constant<int, 1 - PAR>{});
+        if (FULL || kp < k1) fetch(kp + 2);
+        // coarse plane (kp >> 1) + 2, first needed for plane kp + 3 (PAR = 0)
+        if constexpr (PROLONG && PAR == 0) {
+            if (FULL || kp <= k1 - 2) cfetch((kp >> 1) + 2);
+        }
+        if constexpr (PROLONG && PAR == 1) {
+            if (FULL || kp <= k1 - 1) cstore((kp + 3) >> 1);
+        }
+        // delta (and f) of the next step's cells: colour 0 at plane kp,
+        // colour 1 at plane kp - 2
+        const R d0 = d0n, dx = dxn, d1 = d1n, f0 = f0n, fx = fxn, f1 = f1n;
+        if (FULL || (kp >= k0 - 1 && kp <= k1)) {
+            const size_t pl = plane_off<R>(kp, L.logn, L.lognh);
+            d0n = ld(L.d0, pl, coff);
+            if (HASF) f0n = ld(L.f0, pl, coff);
+            if (w < 3) {
+                if (extra) {
+                    dxn = ld(L.d0, pl, coffe);
+                    if (HASF) fxn = ld(L.f0, pl, coffe);
+                }
+            }
+        }
+        if (FULL || (kp >= k0 + 2 && kp <= k1 + 1)) {
+            const size_t pl = plane_off<R>(kp - 2, L.logn, L.lognh);
+            d1n = ld_once(L.d1, pl, coff);
+            if (HASF) f1n = ld_once(L.f1, pl, coff);
+        }
+        // plane views: kp and the two below it
+        const R *A0 = sS[kp & 3][0] + 1, *A1 = sS[(kp - 1) & 3][0] + 1,
+                *A2 = sS[(kp - 2) & 3][0] + 1;
+        // x parity of a colour-0 column of row w in plane kp is (w + kp) & 1;
+        // its complement holds for colour 0 in plane kp - 1 and for colour 1
+        // in plane kp - 2
+        const int ox = o + ((w + PAR + 1) & 1), oy = o + ((w + PAR) & 1);
+        const int t = kp - 1;
+        if (FULL || kp <= k1 + 1) {
+            ZPart<R> a;
+            a.read(A0, A0 + SSLOT, o, ox);
+            if (FULL || kp >= k0) {
+                const bool own = FULL || (t >= k0 && t < k1);
+                XyPart<R> c;
+                c.read(A1, A1 + SSLOT, o, ox);
+                const R nv = update(a, c, P[PAR], d0, f0, own);
+                sC[1 - PAR][o - TXH] = nv;
+                if (own)
+                    __builtin_nontemporal_store(nv, ptr(out0, plane_off<R>(t, L.logn, L.lognh),
+                                                        coff));
+                if (w < 3) {
+                    if (extra) {
+                        const int oex = oe + ((ye + PAR + 1) & 1);
+                        ZPart<R> ae, be;
+                        ae.read(A0, A0 + SSLOT, oe, oex);
+                        be.read(A2, A2 + SSLOT, oe, oex);
+                        c.read(A1, A1 + SSLOT, oe, oex);
+                        sC[1 - PAR][oe - TXH] = update(ae, c, be, dx, fx, false);
+                    }
+                }
+            }
+            P[PAR] = a;
+        }
+        if (FULL || (kp >= k0 + 1 && kp <= k1 + 2)) {
+            const R *B = A2 + SSLOT, *C = sC[PAR] - TXH;
+            ZPart<R> a;
+            a.read(B, C, o, oy);
+            if (FULL || kp >= k0 + 3) {
+                const R nv = update(a, q, Q[PAR], d1, f1, true);
+                __builtin_nontemporal_store(nv, ptr(out1, plane_off<R>(kp - 3, L.logn, L.lognh),
+                                                    coff));
+            }
+            Q[PAR] = a;
+            q.read(B, C, o, ox);
+        }
+        __syncthreads();
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    fetch(k0 - 2);
+    if constexpr (PROLONG) {
+        for (int Z = (k0 >> 1) - 2; Z <= k0 >> 1; ++Z) {
+            cfetch(Z);
+            cstore(Z);
+        }
+        __syncthreads();
+    }
+    stage(k0 - 2, even);
+    fetch(k0 - 1);
+    __syncthreads();
+    int kp = k0 - 2;
+    auto edge = [&](int end) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (; kp < end; kp += 2) {
+            step(kp, even, std::false_type{});
+            step(kp + 1, odd, std::false_type{});
+        }
+    };
+    edge(k0 + 4);
+#pragma unroll 1
+    for (; kp + 1 < k1; kp += 2) {
+        step(kp, even, std::true_type{});
+        step(kp + 1, odd, std::true_type{});
+    }
+    edge(k1 + 3);
+    if (clamp && nclamp) atomicAdd(clamp, (unsigned long long)nclamp);
+}
+
+}  // namespace mgk

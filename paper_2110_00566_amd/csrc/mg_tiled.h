@@ -1,6 +1,7 @@
-// LDS-tiled versions of the three kernels that touch every finest-level cell
-// (colour pass, residual + restriction, prolongation), for levels with at
-// least 128 cells per side.
+// LDS-tiled versions of the kernels that touch every finest-level cell
+// (colour pass, residual + restriction, prolongation, coarse source), for
+// levels with at least 128 cells per side.  The smoothing sweeps of the solves
+// are in mg_sweep.h.
 //
 // A block owns a tile of TX = 64 packed x-columns (one wave wide) and TY = 8
 // rows and marches through a z-chunk.  The planes it needs are staged once in
@@ -231,9 +232,9 @@ __device__ __forceinline__ T tiled_term(const Mod &M, const L_ &L, const NbT<T> 
 
 // New value of a cell in a colour pass: the closed-form update, or for
 // OP_NEWTON the Newton-Gauss-Seidel step on the quadratic form.
-template <int OP, typename R, typename L_>
-__device__ __forceinline__ R tiled_update(const Mod &M, const L_ &L, const NbT<R> &s, R delta,
-                                          R faces, R u, R f, unsigned long long *clamp) {
+template <int OP, typename R, typename L_, typename S_, typename Clamp>
+__device__ __forceinline__ R tiled_update(const Mod &M, const L_ &L, const S_ &s, R delta,
+                                          R faces, R u, R f, Clamp *clamp) {
     if constexpr (OP == OP_NEWTON) {
         return newton_update<R>(M, u, faces, dgp_sigma_over_alpha<R>(M, L, s, delta), f,
                                 (R)L.h2);
@@ -244,37 +245,35 @@ __device__ __forceinline__ R tiled_update(const Mod &M, const L_ &L, const NbT<R
 }
 
 // One colour pass (see k_pass) on an LDS-staged tile.
-template <int OP, typename R>
-__global__ __launch_bounds__(TPB) void k_pass_tiled(Mod M, LvlT<R> L, int c, R *__restrict__ out,
-                                                    const double *fptr, double fscale,
-                                                    unsigned long long *clamp, TileGeom G) {
-    __shared__ __align__(16) R sA[3][TSLOT], sB[3][TSLOT];
+template <int OP>
+__global__ __launch_bounds__(TPB) void k_pass_tiled(Mod M, Lvl L, int c, double *__restrict__ out,
+                                                    TileGeom G) {
+    __shared__ __align__(16) double sA[3][TSLOT], sB[3][TSLOT];
     const size_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int bx = (int)(blk % G.ntx);
     const int by = (int)((blk / G.ntx) % G.nty);
     const int bz = (int)(blk / ((size_t)G.ntx * G.nty));
     const int m0 = bx * TX, j0 = by * TY, k0 = bz * G.kz;
-    const R *A = c ? L.u1 : L.u0;
-    const R *B = c ? L.u0 : L.u1;
-    const R *D = c ? L.d1 : L.d0;
-    const R *F = c ? L.f1 : L.f0;
+    const double *A = c ? L.u1 : L.u0;
+    const double *B = c ? L.u0 : L.u1;
+    const double *D = c ? L.d1 : L.d0;
+    const double *F = c ? L.f1 : L.f0;
     const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-    const R fs = (R)(fptr ? fscale * (*fptr) : 0.0);
     unsigned coff[2];
-    Stage2<R> S;
+    Stage2<double> S;
     S.init(tid, j0, m0, L.logn, L.lognh);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) coff[h] = cell_off<R>(j0 + ty + 4 * h, m0 + tx, L.lognh);
-    auto fetch = [&](int k) { S.fetch(A, B, plane_off<R>(k, L.logn, L.lognh), tid); };
+    for (int h = 0; h < 2; ++h) coff[h] = cell_off<double>(j0 + ty + 4 * h, m0 + tx, L.lognh);
+    auto fetch = [&](int k) { S.fetch(A, B, plane_off<double>(k, L.logn, L.lognh), tid); };
     auto store = [&](int slot) { S.store(sA[slot] + 1, sB[slot] + 1, tid); };
     // own cells' delta and f, one plane ahead
-    R dn[2], fn[2];
+    double dn[2], fn[2];
     auto fetch_cells = [&](int k) {
-        const size_t pl = plane_off<R>(k, L.logn, L.lognh);
+        const size_t pl = plane_off<double>(k, L.logn, L.lognh);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             dn[h] = ld_once(D, pl, coff[h]);
-            fn[h] = F ? ld_once(F, pl, coff[h]) : (R)0;
+            fn[h] = ld_once(F, pl, coff[h]);
         }
     };
     // slot of plane k: (k - k0 + 1) mod 3
@@ -287,7 +286,7 @@ __global__ __launch_bounds__(TPB) void k_pass_tiled(Mod M, LvlT<R> L, int c, R *
     for (int k = k0; k < k0 + G.kz; ++k) {
         const int sm = (k - k0) % 3, s0 = (k - k0 + 1) % 3, sp = (k - k0 + 2) % 3;
         store(sp);
-        const R d0 = dn[0], d1 = dn[1], f0 = fn[0], f1 = fn[1];
+        const double d0 = dn[0], d1 = dn[1], f0 = fn[0], f1 = fn[1];
         __syncthreads();
         if (k + 2 <= k0 + G.kz) fetch(k + 2);
         if (k + 1 < k0 + G.kz) fetch_cells(k + 1);
@@ -296,14 +295,16 @@ __global__ __launch_bounds__(TPB) void k_pass_tiled(Mod M, LvlT<R> L, int c, R *
             const int row = ty + 4 * h;
             const int j = j0 + row;
             const int p = (j + k + c) & 1;
-            const NbT<R> s = lds_nb<R, R>(sA[sm] + 1, sA[s0] + 1, sA[sp] + 1, sB[s0] + 1,
-                                          sB[sm] + 1, sB[sp] + 1, row + 1, tx + 1, p);
-            const R faces = (s.xp + s.xm) + (s.yp + s.ym) + (s.zp + s.zm);
-            const R f = (h ? f1 : f0) + fs;
-            const R nv = tiled_update<OP, R>(M, L, s, h ? d1 : d0, faces,
-                                             sA[s0][1 + (row + 1) * TXH + tx + 1], f, clamp);
+            const Nb s = lds_nb<double, double>(sA[sm] + 1, sA[s0] + 1, sA[sp] + 1, sB[s0] + 1,
+                                                sB[sm] + 1, sB[sp] + 1, row + 1, tx + 1, p);
+            const double faces = (s.xp + s.xm) + (s.yp + s.ym) + (s.zp + s.zm);
+            unsigned neg = 0;
+            const double nv =
+                tiled_update<OP, double>(M, L, s, h ? d1 : d0, faces,
+                                         sA[s0][1 + (row + 1) * TXH + tx + 1], h ? f1 : f0, &neg);
             // streamed: the next reader is a later launch
-            __builtin_nontemporal_store(nv, ptr(out, plane_off<R>(k, L.logn, L.lognh), coff[h]));
+            __builtin_nontemporal_store(nv, ptr(out, plane_off<double>(k, L.logn, L.lognh),
+                                                coff[h]));
         }
         __syncthreads();
     }
@@ -529,209 +530,6 @@ __global__ __launch_bounds__(TPB) void k_prolong_tiled(R *f0, R *f1, int logn, c
         __syncthreads();
     }
     if (REDUCE) block_sum2(bsum[0], bsum[1], partials, blk);
-}
-
-// Prolongation of the coarse correction fused with the first post-smoothing
-// pass (colour 0).  Every staged fine value is corrected on the fly,
-// u + P(uc - rc), colour-0 cells get the closed-form update from the corrected
-// neighbourhood (out0) and colour-1 cells are written corrected (out1).  Both
-// outputs are separate arrays: neighbouring tiles still read the old values.
-//
-// The 27/9/3/1 weights factor into a z part (3/4 own coarse plane, 1/4 the
-// plane on the fine cell's side) times an x-y bilinear part (9, 3, 3, 1 over
-// 16).  A thread keeps the x-y part of the two coarse planes the next staged
-// fine planes need, at its staged positions and for both x parities, in
-// registers; one coarse plane of 68 x 6 values around the tile passes through
-// LDS every second fine plane.  kz (fine planes per block) is even.
-// The Kmouflage instance is held to 3 waves per SIMD (167 registers, no
-// spill; unconstrained it takes 171 and runs 2): its 512^3 solve is 4.5%
-// faster.
-template <int OP, typename R>
-__global__ __launch_bounds__(TPB)
-__attribute__((amdgpu_waves_per_eu(OP == OP_KMO ? 3 : 1))) void k_prolong_pass_tiled(Mod M, LvlT<R> L, R *__restrict__ out0,
-                                                            R *__restrict__ out1, const R *uc0,
-                                                            const R *uc1, const R *rc0,
-                                                            const R *rc1, const double *fptr,
-                                                            double fscale,
-                                                            unsigned long long *clamp, TileGeom G) {
-    constexpr int CW = TX + 4;           // coarse columns m0-2 .. m0+65
-    constexpr int CH = TY / 2 + 2;       // coarse rows j0/2-1 .. j0/2+4
-    constexpr int CPL = CW * CH;
-    constexpr int CLOADS = (CPL + TPB - 1) / TPB;
-    // arithmetic type of the coarse correction: that of the storage (in FP32
-    // storage the correction, small beside phi, needs no FP64)
-    using CT = R;
-    __shared__ R sA[3][TPLANE], sB[3][TPLANE];
-    __shared__ CT sC[CPL];
-    const size_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const int bx = (int)(blk % G.ntx);
-    const int by = (int)((blk / G.ntx) % G.nty);
-    const int bz = (int)(blk / ((size_t)G.ntx * G.nty));
-    const int m0 = bx * TX, j0 = by * TY, k0 = bz * G.kz, K0 = k0 >> 1;
-    const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-    const int lnc = L.logn - 1, ncm1 = (1 << lnc) - 1;
-    const R fs = (R)(fptr ? fscale * (*fptr) : 0.0);
-
-    // coarse difference uc - rc of one coarse plane, via registers into sC
-    CT cu[CLOADS], cr[CLOADS];
-    auto cfetch = [&](int Z) {
-        const int Zw = Z & ncm1;
-#pragma unroll
-        for (int q = 0; q < CLOADS; ++q) {
-            const int e = tid + q * TPB;
-            if (e < CPL) {
-                const int r = e / CW, cI = e - r * CW;
-                const int X = (m0 - 2 + cI) & ncm1;
-                const int Y = ((j0 >> 1) - 1 + r) & ncm1;
-                const size_t idx =
-                    ((size_t)Zw << (2 * lnc - 1)) + ((size_t)Y << (lnc - 1)) + (X >> 1);
-                const bool odd = (X + Y + Zw) & 1;
-                cu[q] = (odd ? uc1 : uc0)[idx];
-                cr[q] = (odd ? rc1 : rc0)[idx];
-            }
-        }
-    };
-    auto cstore = [&]() {
-#pragma unroll
-        for (int q = 0; q < CLOADS; ++q) {
-            const int e = tid + q * TPB;
-            if (e < CPL) sC[e] = cu[q] - cr[q];
-        }
-    };
-    // x-y bilinear part of the coarse plane in sC at the thread's staged
-    // positions, for fine x = 2m (index 0, coarse neighbour m-1) and
-    // x = 2m+1 (index 1, coarse neighbour m+1)
-    CT xlo[TLOADS][2], xhi[TLOADS][2], xnx[TLOADS][2];
-    auto interp = [&](CT (&x)[TLOADS][2]) {
-#pragma unroll
-        for (int q = 0; q < TLOADS; ++q) {
-            const int e = tid + q * TPB;
-            if (e < TPLANE) {
-                const int r = e / TXH, cI = e - r * TXH;
-                const int lr = (r + 1) >> 1, lc = cI + 1;
-                const int ly = (r & 1) ? lr - 1 : lr + 1;   // fine row odd: coarse row above
-                const CT c0 = sC[lr * CW + lc], cm = sC[lr * CW + lc - 1],
-                         cp = sC[lr * CW + lc + 1];
-                const CT d0 = sC[ly * CW + lc], dm = sC[ly * CW + lc - 1],
-                         dp = sC[ly * CW + lc + 1];
-                x[q][0] = (CT)(9.0 / 16.0) * c0 + (CT)(3.0 / 16.0) * cm +
-                          (CT)(3.0 / 16.0) * d0 + (CT)(1.0 / 16.0) * dm;
-                x[q][1] = (CT)(9.0 / 16.0) * c0 + (CT)(3.0 / 16.0) * cp +
-                          (CT)(3.0 / 16.0) * d0 + (CT)(1.0 / 16.0) * dp;
-            }
-        }
-    };
-
-    // raw fine values of the next plane, and own cells' delta and f
-    unsigned soff[TLOADS], coff[2];
-#pragma unroll
-    for (int q = 0; q < TLOADS; ++q) soff[q] = stage_off<R>(tid + q * TPB, j0, m0, L.logn, L.lognh);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) coff[h] = cell_off<R>(j0 + ty + 4 * h, m0 + tx, L.lognh);
-    R ra[TLOADS], rb[TLOADS];
-    auto fetch = [&](int k) {
-        const size_t pl = plane_off<R>(k, L.logn, L.lognh);
-#pragma unroll
-        for (int q = 0; q < TLOADS; ++q) {
-            if (tid + q * TPB < TPLANE) {
-                ra[q] = ld(L.u0, pl, soff[q]);
-                rb[q] = ld(L.u1, pl, soff[q]);
-            }
-        }
-    };
-    // corrected plane k into ring slot; the coarse pair (lo, hi) holds the
-    // plane's own coarse plane (hi for even k, lo for odd k) and its neighbour
-    auto stage = [&](int slot, int k, bool kodd) {
-        const CT wl = kodd ? (CT)0.75 : (CT)0.25, wh = kodd ? (CT)0.25 : (CT)0.75;
-#pragma unroll
-        for (int q = 0; q < TLOADS; ++q) {
-            const int e = tid + q * TPB;
-            if (e < TPLANE) {
-                const int r = e / TXH;
-                const bool p0 = (j0 - 1 + r + k) & 1;   // x parity of the colour-0 value
-                const CT l0 = p0 ? xlo[q][1] : xlo[q][0], l1 = p0 ? xlo[q][0] : xlo[q][1];
-                const CT h0 = p0 ? xhi[q][1] : xhi[q][0], h1 = p0 ? xhi[q][0] : xhi[q][1];
-                sA[slot][e] = ra[q] + (wl * l0 + wh * h0);
-                sB[slot][e] = rb[q] + (wl * l1 + wh * h1);
-            }
-        }
-    };
-    R dn[2], fn[2];
-    auto fetch_cells = [&](int k) {
-        const size_t pl = plane_off<R>(k, L.logn, L.lognh);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            dn[h] = ld_once(L.d0, pl, coff[h]);
-            fn[h] = L.f0 ? ld_once(L.f0, pl, coff[h]) : (R)0;
-        }
-    };
-
-    // coarse planes K0-1, K0 (pair for fine planes k0-1, k0) and K0+1
-    cfetch(K0 - 1);
-    cstore();
-    __syncthreads();
-    interp(xlo);
-    __syncthreads();
-    cfetch(K0);
-    cstore();
-    __syncthreads();
-    interp(xhi);
-    __syncthreads();
-    cfetch(K0 + 1);
-    cstore();
-    __syncthreads();
-    interp(xnx);
-    // slot of fine plane k: (k - k0 + 1) mod 3
-    fetch(k0 - 1);
-    stage(0, k0 - 1, true);
-    fetch(k0);
-    stage(1, k0, false);
-    fetch(k0 + 1);
-    fetch_cells(k0);
-
-    auto step = [&](int k, bool odd) {
-        if (!odd) {
-#pragma unroll
-            for (int q = 0; q < TLOADS; ++q) {
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    xlo[q][b] = xhi[q][b];
-                    xhi[q][b] = xnx[q][b];
-                }
-            }
-        }
-        const int sm = (k - k0) % 3, s0 = (k - k0 + 1) % 3, sp = (k - k0 + 2) % 3;
-        stage(sp, k + 1, !odd);
-        // a new coarse plane (k >> 1) + 2 is needed for fine planes beyond k + 2
-        const bool cnew = odd && (k + 3 <= k0 + G.kz);
-        if (cnew) cstore();
-        const R d0 = dn[0], d1 = dn[1], f0 = fn[0], f1 = fn[1];
-        __syncthreads();
-        if (k + 2 <= k0 + G.kz) fetch(k + 2);
-        if (k + 1 < k0 + G.kz) fetch_cells(k + 1);
-        if (!odd && k + 4 <= k0 + G.kz) cfetch((k >> 1) + 2);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int row = ty + 4 * h;
-            const int j = j0 + row;
-            const int p = (j + k) & 1;
-            const NbT<R> s = lds_nb<R, R>(sA[sm], sA[s0], sA[sp], sB[s0], sB[sm], sB[sp], row + 1,
-                                          tx + 1, p);
-            const size_t pl = plane_off<R>(k, L.logn, L.lognh);
-            const R faces = (s.xp + s.xm) + (s.yp + s.ym) + (s.zp + s.zm);
-            const R f = (h ? f1 : f0) + fs;
-            const R nv = tiled_update<OP, R>(M, L, s, h ? d1 : d0, faces,
-                                             sA[s0][(row + 1) * TXH + tx + 1], f, clamp);
-            __builtin_nontemporal_store(nv, ptr(out0, pl, coff[h]));
-            __builtin_nontemporal_store(sB[s0][(row + 1) * TXH + tx + 1], ptr(out1, pl, coff[h]));
-        }
-        if (cnew) interp(xnx);
-        __syncthreads();
-    };
-    for (int k = k0; k < k0 + G.kz; k += 2) {
-        step(k, false);
-        step(k + 1, true);
-    }
 }
 
 // FAS source on a coarse level (see k_coarse_source) on an LDS-staged tile:
