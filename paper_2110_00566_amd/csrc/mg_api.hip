@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/mgglam.h"
@@ -120,46 +121,49 @@ struct Ctx {
     std::vector<Segment> segs;
     int lev_used = 0;
     double level_ms[MG_LEVELS] = {};
-    // Early read of the cycle's stopping scalars: they are final once the
-    // finest in-cycle residual has been reduced, so they are copied to pinned
-    // host memory at that point and the host decides on the next cycle while
-    // the coarse levels and the post-smoothing still run.
+    // The residual's scalars in pinned host memory (see k_finalize): they are
+    // final once the finest in-cycle residual has been reduced, so the host
+    // decides on the next cycle while the coarse levels and the post-smoothing
+    // still run.  Null: read by a copy after the whole cycle.
     double *pin = nullptr;
-    hipEvent_t pin_ev = nullptr;
-    bool pin_pending = false;
+    unsigned long long *pin_seq = nullptr;   // number of the thread's last reduction
+    bool pin_pending = false;                // it has not been waited for
     Ctx() = default;
     Ctx(const Ctx &) = delete;
     Ctx &operator=(const Ctx &) = delete;
     ~Ctx() {
-        // an early copy still in flight (a call that ended on an error) must
-        // land before the next call on this thread reuses the pinned buffer
-        if (pin_pending) (void)hipEventSynchronize(pin_ev);
-        if (pin_ev) (void)hipEventDestroy(pin_ev);
+        // a store still to come (a call that ended on an error) must land
+        // before the next call on this thread reuses the pinned buffer
+        if (pin_pending) (void)hipStreamSynchronize(st);
+    }
+    double *next_host(unsigned long long &seq) {
+        if (!pin) return nullptr;
+        seq = ++*pin_seq;
+        pin_pending = true;
+        return pin;
     }
 };
 
 // Pinned host buffer for the per-cycle scalars, one per host thread (calls on
 // one thread never overlap), allocated on first use and kept until the
-// process ends.  nullptr if the allocation fails: the solver then reads the
-// scalars after the whole cycle.
-double *pinned_scalars() {
+// process ends, and the number of the thread's last reduction.  Without it
+// (the allocation failed) the solver reads the scalars after the whole cycle.
+void arm_host_scalars(Ctx &C) {
     thread_local double *p = nullptr;
+    thread_local unsigned long long seq = 0;
     if (!p) {
         void *q = nullptr;
-        if (hipHostMalloc(&q, sizeof(double) * S_NSCAL, hipHostMallocDefault) == hipSuccess)
+        if (hipHostMalloc(&q, sizeof(double) * S_NSCAL,
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) ==
+            hipSuccess) {
             p = static_cast<double *>(q);
-        else
+            std::memset(p, 0, sizeof(double) * S_NSCAL);
+        } else {
             (void)hipGetLastError();
+        }
     }
-    return p;
-}
-
-void arm_early_read(Ctx &C) {
-    C.pin = pinned_scalars();
-    if (C.pin && hipEventCreateWithFlags(&C.pin_ev, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        C.pin_ev = nullptr;
-    }
+    C.pin = p;
+    C.pin_seq = &seq;
 }
 
 template <typename R>
@@ -358,8 +362,7 @@ unsigned launch_resid_restrict(const Mod &M, const LvlT<R> &L, const Coefs &Cf, 
                 M, L, fptr, fs, ru0, ru1, rd0, rd1, partials, clamp, G);
         return nb;
     }
-    const size_t ncoarse = (size_t)L.n * L.n * L.n / 8;
-    const unsigned nb = nblocks(ncoarse);
+    const unsigned nb = nblocks((size_t)L.n * L.n * L.n);
     k_resid_restrict<OP, REDUCE, R><<<nb, TPB, 0, st>>>(M, L, Cf, fptr, fs, ru0, ru1, rd0, rd1,
                                                         partials, clamp);
     return nb;
@@ -615,6 +618,15 @@ struct Solver {
         }
     }
 
+    // reduce the finest residual's nb block sums (k_finalize mode 0, 2 or 5)
+    void finalize(unsigned nb, int mode) {
+        const double n = Hh.lv[0].n;
+        unsigned long long seq = 0;
+        double *host = C.profile ? nullptr : C.next_host(seq);
+        k_finalize<<<1, 1024, 0, C.st>>>(C.partials, nb, n * n * n, C.scal, mode, C.kappa, 0, host,
+                                         seq);
+    }
+
     // residual (+ statistics on the finest level) and restriction into l+1
     void resid_restrict(int l) {
         HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
@@ -634,8 +646,7 @@ struct Solver {
                     launch_adj_tiled<ADJ_RESID, true>(C.adj_model, A, 1, nullptr, nullptr,
                                                       nullptr, 0.0, q[0], q[1], q[2], q[3],
                                                       C.partials + 2 * nb, C.st);
-                    k_finalize<<<1, 1024, 0, C.st>>>(C.partials, 2 * nb,
-                                                     (double)H.n * H.n * H.n, C.scal, 2, C.kappa);
+                    finalize(2 * nb, 2);
                 } else {
                     for (int c = 0; c < 2; ++c)
                         launch_adj_tiled<ADJ_RESID, false>(C.adj_model, A, c, nullptr, nullptr,
@@ -650,8 +661,7 @@ struct Solver {
             const unsigned nb = launch_resid_restrict<OP, true, R>(
                 C.M, view(H, with_f), coefs(H), fptr, 1.0, Hc.ru[0], Hc.ru[1], Hc.f[0], Hc.f[1],
                 C.partials, C.clamp, C.st);
-            k_finalize<<<1, 1024, 0, C.st>>>(C.partials, nb, (double)H.n * H.n * H.n, C.scal,
-                                             OP == OP_ADJ ? 2 : 0, C.kappa);
+            finalize(nb, OP == OP_ADJ ? 2 : 0);
         } else {
             launch_resid_restrict<OP, false, R>(C.M, view(H, with_f), coefs(H), fptr, 1.0,
                                                 Hc.ru[0], Hc.ru[1], Hc.f[0], Hc.f[1], C.partials,
@@ -713,7 +723,9 @@ struct Solver {
     }
 
     template <int NL>
-    void launch_tail(const TailArgs<R> &A, size_t lds) {
+    void launch_tail(const TailArgs<R> &A) {
+        constexpr int lds = tail_lds_bytes<OP, R>(NL);
+        static_assert(lds <= 160 * 1024, "tail exceeds the LDS of a CU");
         // once per instantiation and process (thread-safe); a failure stays
         // in the HIP error state and is reported with the solve's launches
         static std::once_flag once;
@@ -740,11 +752,10 @@ struct Solver {
             A.lv[q].ru1 = H.ru[1];
             A.cf[q] = coefs(H);
         }
-        const size_t lds = sizeof(R) * tail_lds_elems(Hh.lv[l].logn, A.nlev);
         switch (A.nlev) {
-            case 1: launch_tail<1>(A, lds); break;
-            case 2: launch_tail<2>(A, lds); break;
-            default: launch_tail<3>(A, lds); break;
+            case 1: launch_tail<1>(A); break;
+            case 2: launch_tail<2>(A); break;
+            default: launch_tail<3>(A); break;
         }
     }
 
@@ -786,7 +797,6 @@ struct Solver {
         }
         for (int s = 0; s < C.nu1; ++s) sweep(l);
         resid_restrict(l);
-        if (l == 0) copy_scal_early();
         coarse_source(l + 1);
         segment(l, e0, mark());
         if (type == 2) {
@@ -809,22 +819,32 @@ struct Solver {
         segment(l, e2, mark());
     }
 
-    // Scalars of the finest in-cycle residual into pinned memory (not in
-    // profile mode, whose event timings need the whole cycle).  No kernel
-    // later in the cycle writes mu or eps^2.
-    void copy_scal_early() {
-        if (C.profile || !C.pin || !C.pin_ev) return;
-        if (hipMemcpyAsync(C.pin, C.scal, sizeof(double) * S_NSCAL, hipMemcpyDeviceToHost,
-                           C.st) == hipSuccess &&
-            hipEventRecord(C.pin_ev, C.st) == hipSuccess)
-            C.pin_pending = true;
-    }
-
+    // The scalars of the last finest residual, from pinned memory as soon as
+    // it is reduced (not in profile mode, whose event timings need the whole
+    // cycle).  The wait ends with an error if the stream fails, or has
+    // finished without the store.
     mg_status read_scal(double *hs) {
         HIPCHK(hipGetLastError());
         if (C.pin_pending) {
+            const unsigned long long want = *C.pin_seq;
+            auto *seq = reinterpret_cast<unsigned long long *>(C.pin) + S_NSCAL - 1;
+            auto arrived = [&] { return __atomic_load_n(seq, __ATOMIC_ACQUIRE) == want; };
+            for (unsigned spin = 1; !arrived(); ++spin) {
+                if (spin & 1023u) {
+                    __builtin_ia32_pause();
+                    continue;
+                }
+                const hipError_t e = hipStreamQuery(C.st);
+                if (e == hipErrorNotReady) {
+                    (void)hipGetLastError();
+                    std::this_thread::yield();
+                    continue;
+                }
+                HIPCHK(e);
+                C.pin_pending = false;
+                if (!arrived()) return fail(MG_ERR_HIP, "the residual did not reach the host");
+            }
             C.pin_pending = false;
-            HIPCHK(hipEventSynchronize(C.pin_ev));
             std::memcpy(hs, C.pin, sizeof(double) * S_NSCAL);
             return MG_OK;
         }
@@ -1076,7 +1096,7 @@ mg_status dc_finish(const mg_opts *o, Ctx &C, DeltaIn delta, double *phi, mg_sta
         k_resid_restrict_tiled<OP, true, false, double, true><<<nbr, TPB, 0, C.st>>>(
             C.M, view(F, false), C.scal + S_MU64, 1.0, Hc.ru[0], Hc.ru[1], Hc.f[0], Hc.f[1],
             C.partials, C.clamp, Gr, G.f[0], G.f[1]);
-        k_finalize<<<1, 1024, 0, C.st>>>(C.partials, nbr, ncell, C.scal, 5, 0.0);
+        S64.finalize(nbr, 5);
         if ((rc = S64.read_scal(hs)) != MG_OK) return rc;
         eps = std::sqrt(hs[S_EPS64]);
         if (cycles32 + cyc < MG_HIST) st->eps_hist[cycles32 + cyc] = eps;
@@ -1159,7 +1179,7 @@ mg_status forward_solve(const mg_opts *o, const Mod &M, const void *delta_p, dou
     C.cycle = o->cycle;
     C.no_sync = o->no_sync != 0;
     Profiler prof(C, o->profile != 0 && !noalloc, 2 * (o->nu_pre + o->nu_post) + 2);
-    if (!noalloc && !C.no_sync) arm_early_read(C);
+    if (!noalloc && !C.no_sync) arm_host_scalars(C);
     reset_scalars(C);
     if (o->precision == MG_FP32) return fp32_solve<OP>(o, C, delta, phi, st, t0);
     HLevel<double> &F = C.h64.lv[0];
@@ -1263,7 +1283,7 @@ mg_status adjoint_solve(const mg_opts *o, const Mod &M, const void *delta_p, con
     C.kappa = 6.0;   // 6/h^2 on the finest level: removes the mean of mu in one pass
     C.adj_model = MODEL;
     Profiler prof(C, false, 0);
-    arm_early_read(C);
+    arm_host_scalars(C);
     reset_scalars(C);
     density_hierarchy<double>(C, delta);
     adj_coefficients<MODEL>(C, phi);

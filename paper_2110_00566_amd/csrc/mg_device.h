@@ -72,11 +72,12 @@ __device__ __forceinline__ CombT<T> comb(const NbT<T> &s) {
             s.zp - s.zm, s.nxy,       s.nxz,       s.nyz};
 }
 
-// Neighbourhood of the cell of colour c at packed (m, j, k).  A holds colour
-// c (edge neighbours), B colour 1-c (face neighbours).
+// Parts of the neighbourhood of the cell of colour c at packed (m, j, k): the
+// face neighbours, from the array B of colour 1-c, and the cross differences,
+// from the array A of colour c.
 template <typename T, typename R>
-__device__ __forceinline__ NbT<T> load_nb(const R *__restrict__ A, const R *__restrict__ B, int c,
-                                          int m, int j, int k, int n, int logn, int lognh) {
+__device__ __forceinline__ void load_faces(NbT<T> &s, const R *__restrict__ B, int c, int m, int j,
+                                           int k, int n, int logn, int lognh) {
     const int nm1 = n - 1, hm1 = (n >> 1) - 1;
     const int p = (j + k + c) & 1;              // i = 2m + p
     const int mp = (m + p) & hm1;               // packed index of i+1
@@ -84,20 +85,35 @@ __device__ __forceinline__ NbT<T> load_nb(const R *__restrict__ A, const R *__re
     const int jp = (j + 1) & nm1, jm = (j - 1) & nm1;
     const int kp = (k + 1) & nm1, km = (k - 1) & nm1;
     const size_t r00 = prow(j, k, logn, lognh);
+    s.xp = (T)B[r00 + mp];
+    s.xm = (T)B[r00 + mm];
+    s.yp = (T)B[prow(jp, k, logn, lognh) + m];
+    s.ym = (T)B[prow(jm, k, logn, lognh) + m];
+    s.zp = (T)B[prow(j, kp, logn, lognh) + m];
+    s.zm = (T)B[prow(j, km, logn, lognh) + m];
+}
+template <typename T, typename R>
+__device__ __forceinline__ void load_cross(NbT<T> &s, const R *__restrict__ A, int c, int m, int j,
+                                           int k, int n, int logn, int lognh) {
+    const int nm1 = n - 1, hm1 = (n >> 1) - 1;
+    const int p = (j + k + c) & 1;
+    const int mp = (m + p) & hm1, mm = (m + p - 1) & hm1;
+    const int jp = (j + 1) & nm1, jm = (j - 1) & nm1;
+    const int kp = (k + 1) & nm1, km = (k - 1) & nm1;
     const size_t rp0 = prow(jp, k, logn, lognh), rm0 = prow(jm, k, logn, lognh);
     const size_t r0p = prow(j, kp, logn, lognh), r0m = prow(j, km, logn, lognh);
     const size_t rpp = prow(jp, kp, logn, lognh), rmm = prow(jm, km, logn, lognh);
     const size_t rpm = prow(jp, km, logn, lognh), rmp = prow(jm, kp, logn, lognh);
-    NbT<T> s;
-    s.xp = (T)B[r00 + mp];
-    s.xm = (T)B[r00 + mm];
-    s.yp = (T)B[rp0 + m];
-    s.ym = (T)B[rm0 + m];
-    s.zp = (T)B[r0p + m];
-    s.zm = (T)B[r0m + m];
     s.nxy = ((T)A[rp0 + mp] + (T)A[rm0 + mm]) - ((T)A[rm0 + mp] + (T)A[rp0 + mm]);
     s.nxz = ((T)A[r0p + mp] + (T)A[r0m + mm]) - ((T)A[r0m + mp] + (T)A[r0p + mm]);
     s.nyz = ((T)A[rpp + m] + (T)A[rmm + m]) - ((T)A[rpm + m] + (T)A[rmp + m]);
+}
+template <typename T, typename R>
+__device__ __forceinline__ NbT<T> load_nb(const R *__restrict__ A, const R *__restrict__ B, int c,
+                                          int m, int j, int k, int n, int logn, int lognh) {
+    NbT<T> s;
+    load_faces(s, B, c, m, j, k, n, logn, lognh);
+    load_cross(s, A, c, m, j, k, n, logn, lognh);
     return s;
 }
 

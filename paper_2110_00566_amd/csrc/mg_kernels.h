@@ -171,63 +171,61 @@ __device__ __forceinline__ void block_sum2(double a, double b, double *partials,
     }
 }
 
-// Residual d = (faces - 6u)/h^2 - K - f (double arithmetic) at the 8 children
-// of coarse cell t, restricted (8-cell mean) together with u.  With REDUCE
-// the sums of d and d^2 accumulate into s1, s2 (finest level: norm and mean).
-// The loop over the 8 children stays rolled (UNR = 1): unrolled, the adjoint
-// and Kmouflage terms need 450-512 registers per lane (one wave per SIMD,
-// with spills; the adjoint residual took 11.8 ms at 512^3, 3.8 ms rolled) and
-// the single-workgroup tail spills at its 128-register cap.
-template <int OP, bool REDUCE, typename R, int UNR = 1>
-__device__ __forceinline__ void dev_resid_restrict(const Mod &M, const LvlT<R> &L, const Coefs &Cf,
-                                                   const double *fptr, double fscale, R *ru0,
-                                                   R *ru1, R *rd0, R *rd1,
-                                                   unsigned long long *clamp, size_t t, double &s1,
-                                                   double &s2) {
-    const int lnc = L.logn - 1, nc = 1 << lnc;
-    const size_t ncoarse = (size_t)1 << (3 * lnc);
-    if (t < ncoarse) {
-        const int I = (int)(t & (nc - 1));
-        const int J = (int)((t >> lnc) & (nc - 1));
-        const int K = (int)(t >> (2 * lnc));
-        double sd = 0.0, su = 0.0;
-        const double inv_h2 = 1.0 / L.h2;
-#pragma unroll UNR
-        for (int q = 0; q < 8; ++q) {
-            const int a = q & 1, b = (q >> 1) & 1, cc = q >> 2;
-            const int j = 2 * J + b, k = 2 * K + cc;
-            const int col = (a + b + cc) & 1;
-            double faces;
-            double term = cell_term<OP, double, R>(M, L, Cf, col, I, j, k, faces, clamp);
-            const size_t idx = prow(j, k, L.logn, L.lognh) + I;
-            const double u = (double)(col ? L.u1 : L.u0)[idx];
-            if constexpr (OP == OP_NEWTON) term = newton_term(M, term, (faces - 6.0 * u) * inv_h2);
-            const double d = (faces - 6.0 * u) * inv_h2 - term
-                           - rhs_at<double, R>(L, col, idx, fptr, fscale);
-            sd += d;
-            su += u;
-            if (REDUCE) {
-                s1 += d;
-                s2 += d * d;
-            }
-        }
-        const int ccol = (I + J + K) & 1;
-        const size_t cidx = ((size_t)K << (2 * lnc - 1)) + ((size_t)J << (lnc - 1)) + (I >> 1);
-        (ccol ? ru1 : ru0)[cidx] = (R)(0.125 * su);
-        (ccol ? rd1 : rd0)[cidx] = (R)(0.125 * sd);
-    }
-}
-
+// Residual d = (faces - 6u)/h^2 - K - f (double arithmetic) of every cell,
+// restricted (8-cell mean) together with u.  With REDUCE the block sums of d
+// and d^2 go to partials (finest level: norm and mean).  A block takes 32
+// coarse cells, a thread one child: waves 0 and 1 the four children of colour
+// 0 of 16 coarse cells each, waves 2 and 3 those of colour 1 (the colour, and
+// with it every array, is uniform in a wave).  The means are then summed child
+// by child in a fixed order.  These levels (<= 64^3) are bound by latency: one
+// thread per coarse cell, its eight children one after the other, took 10.4 us
+// at 32^3 and 64^3.
 template <int OP, bool REDUCE, typename R>
 __global__ __launch_bounds__(TPB) void k_resid_restrict(Mod M, LvlT<R> L, Coefs Cf,
                                                         const double *fptr, double fscale, R *ru0,
                                                         R *ru1, R *rd0, R *rd1, double *partials,
                                                         unsigned long long *clamp) {
+    __shared__ double sd[8][32], su[8][32];
     const size_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const size_t t = blk * TPB + threadIdx.x;
-    double s1 = 0.0, s2 = 0.0;
-    dev_resid_restrict<OP, REDUCE, R>(M, L, Cf, fptr, fscale, ru0, ru1, rd0, rd1, clamp, t, s1, s2);
-    if (REDUCE) block_sum2(s1, s2, partials, blk);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = w >> 1, cell = (w & 1) * 16 + (lane & 15);
+    // children of colour 0: 0, 3, 5, 6; of colour 1: 1, 2, 4, 7 (bits x, y, z)
+    const int qb = lane >> 4, q = qb < 2 ? (col ? 1 + qb : 3 * qb) : (col ? 3 * qb - 2 : 3 + qb);
+    const int lnc = L.logn - 1, nc = 1 << lnc;
+    const size_t t = blk * 32 + cell;
+    auto coords = [&](size_t tc, int &I, int &J, int &K) {
+        I = (int)(tc & (nc - 1));
+        J = (int)((tc >> lnc) & (nc - 1));
+        K = (int)(tc >> (2 * lnc));
+    };
+    int I, J, K;
+    coords(t, I, J, K);
+    const int j = 2 * J + ((q >> 1) & 1), k = 2 * K + (q >> 2);
+    const double inv_h2 = 1.0 / L.h2;
+    double faces;
+    double term = cell_term<OP, double, R>(M, L, Cf, col, I, j, k, faces, clamp);
+    const size_t idx = prow(j, k, L.logn, L.lognh) + I;
+    const double u = (double)(col ? L.u1 : L.u0)[idx];
+    if constexpr (OP == OP_NEWTON) term = newton_term(M, term, (faces - 6.0 * u) * inv_h2);
+    const double d = (faces - 6.0 * u) * inv_h2 - term - rhs_at<double, R>(L, col, idx, fptr, fscale);
+    sd[q][cell] = d;
+    su[q][cell] = u;
+    __syncthreads();
+    if (threadIdx.x < 32) {
+        const size_t tc = blk * 32 + threadIdx.x;
+        coords(tc, I, J, K);
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            a += sd[e][threadIdx.x];
+            b += su[e][threadIdx.x];
+        }
+        const int ccol = (I + J + K) & 1;
+        const size_t cidx = ((size_t)K << (2 * lnc - 1)) + ((size_t)J << (lnc - 1)) + (I >> 1);
+        (ccol ? ru1 : ru0)[cidx] = (R)(0.125 * b);
+        (ccol ? rd1 : rd0)[cidx] = (R)(0.125 * a);
+    }
+    if (REDUCE) block_sum2(d, d * d, partials, blk);
 }
 
 // Starting value of the finest level's bordering scalar mu: the mean of
@@ -259,11 +257,7 @@ __global__ __launch_bounds__(64) void k_mu_estimate(Mod M, LvlT<R> L, Coefs Cf, 
 template <int OP, typename R>
 __device__ __forceinline__ void dev_coarse_source(const Mod &M, const LvlT<R> &Lc, const Coefs &Cf,
                                                   R *s0, R *s1, R *u0, R *u1, const double *shift,
-                                                  size_t t) {
-    const size_t half = (size_t)1 << (3 * Lc.logn - 1);
-    if (t >= 2 * half) return;
-    const int c = t >= half;
-    const size_t tt = t - (c ? half : 0);
+                                                  int c, size_t tt) {
     const int m = (int)(tt & ((1u << Lc.lognh) - 1));
     const int j = (int)((tt >> Lc.lognh) & (Lc.n - 1));
     const int k = (int)(tt >> (Lc.lognh + Lc.logn));
@@ -281,7 +275,10 @@ template <int OP, typename R>
 __global__ __launch_bounds__(TPB) void k_coarse_source(Mod M, LvlT<R> Lc, Coefs Cf, R *s0, R *s1,
                                                        R *u0, R *u1, const double *shift) {
     const size_t t = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
-    dev_coarse_source<OP, R>(M, Lc, Cf, s0, s1, u0, u1, shift, t);
+    const size_t half = (size_t)1 << (3 * Lc.logn - 1);
+    if (t >= 2 * half) return;
+    const int c = t >= half;
+    dev_coarse_source<OP, R>(M, Lc, Cf, s0, s1, u0, u1, shift, c, t - (c ? half : 0));
 }
 
 // u_fine += P(uc - rc) with the cell-centred trilinear weights 27/9/3/1 (/64).
@@ -406,9 +403,15 @@ __global__ __launch_bounds__(TPB) void k_sum(const R *a0, const R *a1, size_t nh
 // colours' sums; mode 4: both colours' sums at once (first and second
 // components); mode 5: mode 0 for the FP64 residual of the defect-correction
 // solve (S_MU64 and S_EPS64).  Summation order is fixed.
+//
+// host: pinned host memory (or null).  The residual's scalars are stored there
+// too, then seq into host[S_NSCAL - 1]: the host waits for that number, with
+// no copy or event on the stream (they cost 14 us per cycle of a 32^3 solve).
 __global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_t nblocks,
                                                    double ncells, double *scal, int mode,
-                                                   double kappa, int colour = 0) {
+                                                   double kappa, int colour = 0,
+                                                   double *host = nullptr,
+                                                   unsigned long long seq = 0) {
     __shared__ double sa[16], sb[16];
     double a = 0.0, b = 0.0;
     for (size_t q = threadIdx.x; q < nblocks; q += 1024) {
@@ -432,19 +435,31 @@ __global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_
         }
         const double mean = x / ncells, msq = y / ncells;
         if (mode == 0) {
-            scal[S_MU] += mean;
+            const double mu = scal[S_MU] + mean;
+            scal[S_MU] = mu;
             scal[S_SHIFT] = mean;
-            const double v = msq - mean * mean;
-            scal[S_EPS2] = v < 0.0 ? 0.0 : v;   // keeps NaN
+            double v = msq - mean * mean;
+            v = v < 0.0 ? 0.0 : v;   // keeps NaN
+            scal[S_EPS2] = v;
+            if (host) {
+                host[S_MU] = mu;
+                host[S_EPS2] = v;
+            }
         } else if (mode == 1) {
             scal[S_MEAN] = mean;
         } else if (mode == 3) {
             scal[S_CSUM0 + colour] = x;
             scal[S_MEAN] = (scal[S_CSUM0] + scal[S_CSUM1]) / ncells;
         } else if (mode == 5) {
-            scal[S_MU64] += mean;
-            const double v = msq - mean * mean;
-            scal[S_EPS64] = v < 0.0 ? 0.0 : v;   // keeps NaN
+            const double mu = scal[S_MU64] + mean;
+            scal[S_MU64] = mu;
+            double v = msq - mean * mean;
+            v = v < 0.0 ? 0.0 : v;   // keeps NaN
+            scal[S_EPS64] = v;
+            if (host) {
+                host[S_MU64] = mu;
+                host[S_EPS64] = v;
+            }
         } else if (mode == 4) {
             scal[S_CSUM0] = x;
             scal[S_CSUM1] = y;
@@ -452,9 +467,17 @@ __global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_
         } else {
             const double km = kappa * scal[S_MEAN];
             scal[S_SHIFT] = 0.0;
-            const double v = msq - 2.0 * km * mean + km * km;
-            scal[S_EPS2] = v < 0.0 ? 0.0 : v;   // keeps NaN
+            double v = msq - 2.0 * km * mean + km * km;
+            v = v < 0.0 ? 0.0 : v;   // keeps NaN
+            scal[S_EPS2] = v;
+            if (host) {
+                host[S_MU] = 0.0;
+                host[S_EPS2] = v;
+            }
         }
+        if (host)
+            __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + S_NSCAL - 1, seq,
+                               __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -495,6 +518,13 @@ __global__ __launch_bounds__(TPB) void k_residual(Mod M, Lvl L, Coefs Cf, const 
 // barriers between phases instead of one launch per phase.  A colour pass
 // first computes every new value of the colour into registers, then writes
 // them in place after a barrier, so all cells see the pre-pass state.
+//
+// One workgroup uses one of the 256 CUs, so what bounds the tail is the
+// latency of its serial phases.  Level sizes are compile-time constants (the
+// coarsest level is 4^3), and every phase gives each thread a single cell at
+// a time: the residual is evaluated per fine cell into LDS and summed over
+// the 8 children afterwards (a thread that evaluated the 8 children of its
+// coarse cell one after the other kept at most half of the threads busy).
 constexpr int TAIL_THREADS = 1024;
 constexpr int TAIL_MAX_N = 16;   // <= 2048 cells per colour: 2 per thread
 constexpr int TAIL_MAX_LEVELS = 3;
@@ -513,143 +543,345 @@ struct TailArgs {
     Coefs cf[TAIL_MAX_LEVELS];
 };
 
+// LDS layout, in order: per level u, f (and d, or for the adjoint the
+// coefficient arrays of the levels below 16^3), R u below the first level;
+// then the residuals (FP64) of the first level's cells.
+template <int OP>
+__host__ __device__ constexpr int tail_level_arrays(int logn, bool first) {
+    // half-level arrays: u 2, f 2, d 2 or 18 coefficient halves, R u 2
+    return 4 + (OP == OP_ADJ ? (logn < 4 ? 18 : 0) : 2) + (first ? 0 : 2);
+}
+// Values before level lv (of nl).
+template <int OP>
+__host__ __device__ constexpr int tail_offset(int nl, int lv) {
+    int tot = 0;
+    for (int q = 0; q < lv; ++q) {
+        const int logn = 1 + nl - q;
+        tot += tail_level_arrays<OP>(logn, q == 0) * (1 << (3 * logn - 1));
+    }
+    return tot;
+}
 template <int OP, typename R>
-__device__ void tail_pass(const Mod &M, const TailLv<R> &T, const Coefs &Cf, int c) {
-    const LvlT<R> &L = T.L;
-    const int half = 1 << (3 * L.logn - 1);
-    R nv[2];
+__host__ __device__ constexpr int tail_lds_bytes(int nl) {
+    const int tot = tail_offset<OP>(nl, nl);
+    return tot * (int)sizeof(R) + (nl > 1 ? (1 << (3 * (nl + 1))) * (int)sizeof(double) : 0);
+}
+
+// The thread index, opaque to the compiler: the addresses of a phase are formed
+// in that phase.  (Formed for all phases ahead of their loops they do not fit
+// the 128 registers of a 1024-thread block: 500 bytes per lane of scratch.)
+__device__ __forceinline__ int tail_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <int LOGN>
+__device__ __forceinline__ void tail_cell(int t, int &m, int &j, int &k) {
+    m = t & ((1 << (LOGN - 1)) - 1);
+    j = (t >> (LOGN - 1)) & ((1 << LOGN) - 1);
+    k = t >> (2 * LOGN - 1);
+}
+
+// New value of the cell of colour c at packed index t.
+template <int OP, int LOGN, typename R>
+__device__ __forceinline__ R tail_new(const Mod &M, const LvlT<R> &L, const Coefs &Cf, int c,
+                                      int t) {
+    int m, j, k;
+    tail_cell<LOGN>(t, m, j, k);
+    R faces;
+    const R K = cell_term<OP, R, R>(M, L, Cf, c, m, j, k, faces, nullptr);
+    const R f = (c ? L.f1 : L.f0)[t];
+    if constexpr (OP == OP_NEWTON)
+        return newton_update<R>(M, (c ? L.u1 : L.u0)[t], faces, K, f, (R)L.h2);
+    else
+        return (faces - (R)L.h2 * (K + f)) * (R)(1.0 / 6.0);
+}
+
+template <int OP, int LOGN, typename R>
+__device__ __forceinline__ void tail_sweeps(const Mod &M, const LvlT<R> &L, const Coefs &Cf,
+                                            int count) {
+    constexpr int HALF = 1 << (3 * LOGN - 1), CNT = (HALF + TAIL_THREADS - 1) / TAIL_THREADS;
+#pragma unroll 1
+    for (int s = 0; s < count; ++s) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int t = threadIdx.x + q * TAIL_THREADS;
-        if (t < half) {
-            const int m = t & ((1 << L.lognh) - 1);
-            const int j = (t >> L.lognh) & (L.n - 1);
-            const int k = t >> (L.lognh + L.logn);
-            R faces;
-            const R K = cell_term<OP, R, R>(M, L, Cf, c, m, j, k, faces, nullptr);
-            const R f = (c ? L.f1 : L.f0)[t];
-            if constexpr (OP == OP_NEWTON)
-                nv[q] = newton_update<R>(M, (c ? L.u1 : L.u0)[t], faces, K, f, (R)L.h2);
-            else
-                nv[q] = (faces - (R)L.h2 * (K + f)) * (R)(1.0 / 6.0);
+        for (int c = 0; c < 2; ++c) {
+            R nv[CNT];
+            const int tid = tail_tid();
+#pragma unroll
+            for (int q = 0; q < CNT; ++q) {
+                const int t = tid + q * TAIL_THREADS;
+                if (HALF % TAIL_THREADS == 0 || t < HALF)
+                    nv[q] = tail_new<OP, LOGN, R>(M, L, Cf, c, t);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < CNT; ++q) {
+                const int t = tid + q * TAIL_THREADS;
+                if (HALF % TAIL_THREADS == 0 || t < HALF) (c ? L.u1 : L.u0)[t] = nv[q];
+            }
+            __syncthreads();
         }
     }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int t = threadIdx.x + q * TAIL_THREADS;
-        if (t < half) (c ? L.u1 : L.u0)[t] = nv[q];
-    }
-    __syncthreads();
 }
 
+// The sweeps of the 4^3 level (32 cells per colour) on the first wavefront
+// alone: a lane per cell, and no workgroup barrier between passes.  A
+// wavefront's LDS reads and writes take effect in program order, so every
+// read of a pass precedes its writes and follows the previous pass's writes,
+// as in tail_sweeps.
 template <int OP, typename R>
-__device__ void tail_sweeps(const Mod &M, const TailLv<R> &T, const Coefs &Cf, int count) {
-    for (int s = 0; s < count; ++s) {
-        tail_pass<OP, R>(M, T, Cf, 0);
-        tail_pass<OP, R>(M, T, Cf, 1);
-    }
-}
-
-// The sweeps of a level with at most 64 cells per colour (the 4^3 level) on
-// the first wavefront alone: a lane per cell, and no workgroup barrier
-// between passes.  A wavefront's LDS reads and writes take effect in program
-// order, so every read of a pass precedes its writes and follows the previous
-// pass's writes, as in tail_pass.
-template <int OP, typename R>
-__device__ void tail_sweeps_wave(const Mod &M, const TailLv<R> &T, const Coefs &Cf, int count) {
-    const LvlT<R> &L = T.L;
-    const int half = 1 << (3 * L.logn - 1);
-    const int t = threadIdx.x;
-    if (t < 64) {
-        const int m = t & ((1 << L.lognh) - 1);
-        const int j = (t >> L.lognh) & (L.n - 1);
-        const int k = t >> (L.lognh + L.logn);
-        for (int s = 0; s < count; ++s) {
+__device__ __forceinline__ void tail_sweeps_wave(const Mod &M, const LvlT<R> &L, const Coefs &Cf,
+                                                 int count) {
+    if (threadIdx.x < 32) {
+        int t = threadIdx.x;
+        if constexpr (OP == OP_ADJ) {
+#pragma unroll 1
+            for (int s = 0; s < count; ++s) {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                R nv = (R)0;
-                if (t < half) {
-                    R faces;
-                    const R K = cell_term<OP, R, R>(M, L, Cf, c, m, j, k, faces, nullptr);
-                    const R f = (c ? L.f1 : L.f0)[t];
-                    if constexpr (OP == OP_NEWTON)
-                        nv = newton_update<R>(M, (c ? L.u1 : L.u0)[t], faces, K, f, (R)L.h2);
-                    else
-                        nv = (faces - (R)L.h2 * (K + f)) * (R)(1.0 / 6.0);
+                for (int c = 0; c < 2; ++c) {
+                    t = tail_tid();   // 18 coefficients per pass: no room for kept addresses
+                    const R nv = tail_new<OP, 2, R>(M, L, Cf, c, t);
+                    __builtin_amdgcn_wave_barrier();
+                    (c ? L.u1 : L.u0)[t] = nv;
+                    __builtin_amdgcn_wave_barrier();
                 }
-                __builtin_amdgcn_wave_barrier();
-                if (t < half) (c ? L.u1 : L.u0)[t] = nv;
-                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            // A pass waits for the face values that the previous pass wrote;
+            // its own colour's cross differences are two passes old and are
+            // read ahead, beside the previous pass.
+            int m, j, k;
+            tail_cell<2>(t, m, j, k);
+            const R d[2] = {L.d0[t], L.d1[t]}, f[2] = {L.f0[t], L.f1[t]};
+            NbT<R> s[2];
+            load_cross(s[0], L.u0, 0, m, j, k, 4, 2, 1);
+#pragma unroll 1
+            for (int q = 0; q < count; ++q) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    R *u = c ? L.u1 : L.u0;
+                    const R *o = c ? L.u0 : L.u1;
+                    load_faces(s[c], o, c, m, j, k, 4, 2, 1);
+                    load_cross(s[c ^ 1], o, c ^ 1, m, j, k, 4, 2, 1);
+                    const R faces = (s[c].xp + s[c].xm) + (s[c].yp + s[c].ym) +
+                                    (s[c].zp + s[c].zm);
+                    R nv;
+                    if constexpr (OP == OP_NEWTON)
+                        nv = newton_update<R>(M, u[t], faces,
+                                              dgp_sigma_over_alpha<R>(M, L, s[c], d[c]), f[c],
+                                              (R)L.h2);
+                    else
+                        nv = (faces - (R)L.h2 * (model_term<OP, R>(
+                                                     M, L, s[c], d[c],
+                                                     (unsigned long long *)nullptr) +
+                                                 f[c])) *
+                             (R)(1.0 / 6.0);
+                    __builtin_amdgcn_wave_barrier();
+                    u[t] = nv;
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
         }
     }
     __syncthreads();
 }
 
-// Elements of LDS the tail needs for levels l0 .. (u, d, f of every level,
-// R u of every level below the first).
-__host__ __device__ inline int tail_lds_elems(int logn0, int nl) {
-    int tot = 0;
-    for (int q = 0; q < nl; ++q) tot += (q ? 8 : 6) * (1 << (3 * (logn0 - q) - 1));
-    return tot;
+// FAS transfer to the next tail level: residual of every cell (double) into
+// res, 8-cell means R u and R d, coarse source S = L(R u) - R d, u = R u.
+template <int OP, int LOGN, typename R>
+__device__ __forceinline__ void tail_restrict(const Mod &M, const LvlT<R> &L, const Coefs &Cf,
+                                              const LvlT<R> &Lc, const Coefs &Cc, R *ru0, R *ru1,
+                                              double *res) {
+    constexpr int HALF = 1 << (3 * LOGN - 1), CNT = (HALF + TAIL_THREADS - 1) / TAIL_THREADS;
+    constexpr int LC = LOGN - 1, NC3 = 1 << (3 * LC);
+    const double inv_h2 = 1.0 / L.h2;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int tid = tail_tid();
+#pragma unroll 1
+        for (int q = 0; q < CNT; ++q) {
+            const int t = tid + q * TAIL_THREADS;
+            if (HALF % TAIL_THREADS == 0 || t < HALF) {
+                int m, j, k;
+                tail_cell<LOGN>(t, m, j, k);
+                double faces;
+                double term = cell_term<OP, double, R>(M, L, Cf, c, m, j, k, faces, nullptr);
+                const double u = (double)(c ? L.u1 : L.u0)[t];
+                if constexpr (OP == OP_NEWTON)
+                    term = newton_term(M, term, (faces - 6.0 * u) * inv_h2);
+                res[c * HALF + t] = (faces - 6.0 * u) * inv_h2 - term - (double)(c ? L.f1 : L.f0)[t];
+            }
+        }
+    }
+    __syncthreads();
+    const int t = tail_tid();
+    static_assert(NC3 <= TAIL_THREADS, "one coarse cell per thread");
+    R *S0 = const_cast<R *>(Lc.f0), *S1 = const_cast<R *>(Lc.f1);
+    if (t < NC3) {
+        const int I = t & ((1 << LC) - 1), J = (t >> LC) & ((1 << LC) - 1), K = t >> (2 * LC);
+        double sd = 0.0, su = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int a = q & 1, b = (q >> 1) & 1, cc = q >> 2, col = (a + b + cc) & 1;
+            const int idx = ((2 * K + cc) << (2 * LOGN - 1)) + ((2 * J + b) << (LOGN - 1)) + I;
+            sd += res[col * HALF + idx];
+            su += (double)(col ? L.u1 : L.u0)[idx];
+        }
+        const int cidx = (K << (2 * LC - 1)) + (J << (LC - 1)) + (I >> 1);
+        const bool odd = (I + J + K) & 1;
+        (odd ? ru1 : ru0)[cidx] = (R)(0.125 * su);
+        (odd ? S1 : S0)[cidx] = (R)(0.125 * sd);
+    }
+    __syncthreads();
+    if (t < NC3) {
+        LvlT<R> Lr = Lc;
+        Lr.u0 = ru0;
+        Lr.u1 = ru1;
+        constexpr int HC = NC3 / 2;
+        auto source = [&](int c, int tt) __attribute__((always_inline)) {
+            dev_coarse_source<OP, R>(M, Lr, Cc, S0, S1, Lc.u0, Lc.u1, nullptr, c, (size_t)tt);
+        };
+        if constexpr (OP == OP_ADJ) {   // the coefficient pointers need a constant colour
+            if (t < HC)
+                source(0, t);
+            else
+                source(1, t - HC);
+        } else {
+            source(t >= HC, t & (HC - 1));
+        }
+    }
+    __syncthreads();
 }
 
-// FAS transfer from tail level l to l+1: residual, R u and R d, coarse source.
-template <int OP, int NL, typename R>
-__device__ __forceinline__ void tail_restrict(const Mod &M, TailLv<R> (&T)[NL],
-                                              const Coefs (&Cf)[NL], int l) {
-    TailLv<R> &Tc = T[l + 1];
-    double s1 = 0.0, s2 = 0.0;
-    const int ncoarse = 1 << (3 * Tc.L.logn);
-    for (int t = threadIdx.x; t < ncoarse; t += TAIL_THREADS)
-        dev_resid_restrict<OP, false, R>(M, T[l].L, Cf[l], nullptr, 0.0, Tc.ru0, Tc.ru1,
-                                         const_cast<R *>(Tc.L.f0), const_cast<R *>(Tc.L.f1),
-                                         nullptr, (size_t)t, s1, s2);
+// u_fine += P(uc - rc) (see dev_prolong; u: both colours, one after the
+// other), from the correction e in natural order.
+template <int LOGN, typename R>
+__device__ __forceinline__ void tail_prolong(R *u, const R *uc0, const R *uc1, const R *rc0,
+                                             const R *rc1, double *e) {
+    constexpr int LC = LOGN - 1, NCM = (1 << LC) - 1, HALF = 1 << (3 * LOGN - 1);
+    const int t = tail_tid();
+    if (t < (1 << (3 * LC))) {
+        const int I = t & NCM, J = (t >> LC) & NCM, K = t >> (2 * LC), i = t >> 1;
+        e[t] = ((I + J + K) & 1) ? (double)uc1[i] - (double)rc1[i]
+                                 : (double)uc0[i] - (double)rc0[i];
+    }
     __syncthreads();
-    LvlT<R> Lr = Tc.L;
-    Lr.u0 = Tc.ru0;
-    Lr.u1 = Tc.ru1;
-    for (int t = threadIdx.x; t < ncoarse; t += TAIL_THREADS)
-        dev_coarse_source<OP, R>(M, Lr, Cf[l + 1], const_cast<R *>(Tc.L.f0),
-                                 const_cast<R *>(Tc.L.f1), Tc.L.u0, Tc.L.u1, nullptr, (size_t)t);
+    constexpr int CNT = 2 * HALF < TAIL_THREADS ? 1 : 2 * HALF / TAIL_THREADS;
+#pragma unroll
+    for (int q = 0; q < CNT; ++q) {
+        const int tt = t + q * TAIL_THREADS, c = tt >= HALF;
+        if (CNT > 1 || tt < 2 * HALF) {
+            int m, j, k;
+            tail_cell<LOGN>(tt & (HALF - 1), m, j, k);
+            const int p = (j + k + c) & 1;   // i = 2m + p, parent I = m
+            const int I2 = (m + (p ? 1 : -1)) & NCM;
+            const int J = j >> 1, J2 = (J + ((j & 1) ? 1 : -1)) & NCM;
+            const int K = k >> 1, K2 = (K + ((k & 1) ? 1 : -1)) & NCM;
+            double acc = 0.0;
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                const int a = o & 1, b = (o >> 1) & 1, cc = o >> 2;
+                const double w = (a ? 1.0 : 3.0) * (b ? 1.0 : 3.0) * (cc ? 1.0 : 3.0);
+                acc += w * e[((((cc ? K2 : K) << LC) + (b ? J2 : J)) << LC) + (a ? I2 : m)];
+            }
+            u[tt] = (R)((double)u[tt] + acc * (1.0 / 64.0));
+        }
+    }
     __syncthreads();
 }
+
+// Tail level LV of a launch with its fields in LDS.
+template <int OP, int NL, int LV, typename R>
+struct TailView {
+    static constexpr int LOGN = 1 + NL - LV, HALF = 1 << (3 * LOGN - 1);
+    LvlT<R> L;
+    R *f0, *f1, *d0, *d1, *ru0, *ru1;   // d0: also the first LDS coefficient array
+    Coefs cf;
+    __device__ __forceinline__ TailView(const TailArgs<R> &A, R *lds) {
+        R *p = lds + tail_offset<OP>(NL, LV);
+        L = A.lv[LV].L;
+        L.n = 1 << LOGN;
+        L.logn = LOGN;
+        L.lognh = LOGN - 1;
+        L.u0 = p;
+        L.u1 = p + HALF;
+        L.f0 = f0 = p + 2 * HALF;
+        L.f1 = f1 = p + 3 * HALF;
+        L.d0 = d0 = p + 4 * HALF;
+        L.d1 = d1 = p + 5 * HALF;
+        ru0 = p + (tail_level_arrays<OP>(LOGN, true)) * HALF;
+        ru1 = ru0 + HALF;
+        if constexpr (OP == OP_ADJ) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    cf.c[i][c] = LOGN < 4 ? (const double *)(d0 + (2 * i + c) * HALF)
+                                          : A.cf[LV].c[i][c];
+            }
+        }
+    }
+    // The level's inputs, through registers: every load of a launch's levels
+    // is in flight before the first is waited for.
+    static constexpr int NIN = (OP == OP_ADJ ? (LOGN < 4 ? 18 : 0) : 2) + (LV == 0 ? 4 : 0);
+    static constexpr int CNT = (HALF + TAIL_THREADS - 1) / TAIL_THREADS;
+    struct In {
+        R v[NIN > 0 ? NIN * CNT : 1];
+    };
+    static __device__ __forceinline__ const R *source(const TailArgs<R> &A, int i) {
+        const LvlT<R> &G = A.lv[LV].L;
+        constexpr int NF = LV == 0 ? 4 : 0;
+        if (i < NF) return i == 0 ? G.u0 : i == 1 ? G.u1 : i == 2 ? G.f0 : G.f1;
+        if (OP != OP_ADJ) return i == NF ? G.d0 : G.d1;
+        return (const R *)A.cf[LV].c[(i - NF) >> 1][(i - NF) & 1];
+    }
+    __device__ __forceinline__ void fetch(const TailArgs<R> &A, In &in) const {
+#pragma unroll
+        for (int i = 0; i < NIN; ++i) {
+            const R *src = source(A, i);
+#pragma unroll
+            for (int q = 0; q < CNT; ++q) {
+                const int t = threadIdx.x + q * TAIL_THREADS;
+                if (HALF % TAIL_THREADS == 0 || t < HALF) in.v[i * CNT + q] = src[t];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(const In &in) const {
+#pragma unroll
+        for (int i = 0; i < NIN; ++i) {
+            // the first level's u and f lead its arrays, the rest starts at d0
+            R *dst = L.u0 + (LV == 0 ? i : i + 4) * HALF;
+#pragma unroll
+            for (int q = 0; q < CNT; ++q) {
+                const int t = threadIdx.x + q * TAIL_THREADS;
+                if (HALF % TAIL_THREADS == 0 || t < HALF) dst[t] = in.v[i * CNT + q];
+            }
+        }
+    }
+};
 
 // One cycle (0 V, 1 F, 2 W) on tail level LV, recursing at compile time.
 template <int OP, int NL, int LV, typename R>
-__device__ __forceinline__ void tail_cycle(const Mod &M, TailLv<R> (&T)[NL], const Coefs (&Cf)[NL],
-                           const TailArgs<R> &A, int type) {
+__device__ __forceinline__ void tail_cycle(const Mod &M, const TailArgs<R> &A, R *lds, int type) {
+    const TailView<OP, NL, LV, R> T(A, lds);
+    constexpr int LOGN = 1 + NL - LV;
     if constexpr (LV == NL - 1) {
-        if (T[LV].L.n == 4)
-            tail_sweeps_wave<OP, R>(M, T[LV], Cf[LV], A.nuc);
-        else
-            tail_sweeps<OP, R>(M, T[LV], Cf[LV], A.nuc);
+        tail_sweeps_wave<OP, R>(M, T.L, T.cf, A.nuc);
     } else {
-        tail_sweeps<OP, R>(M, T[LV], Cf[LV], A.nu1);
-        tail_restrict<OP, NL, R>(M, T, Cf, LV);
-        if (type == 2) {
-            tail_cycle<OP, NL, LV + 1, R>(M, T, Cf, A, 2);
-            tail_cycle<OP, NL, LV + 1, R>(M, T, Cf, A, 2);
-        } else if (type == 1) {
-            tail_cycle<OP, NL, LV + 1, R>(M, T, Cf, A, 1);
-            tail_cycle<OP, NL, LV + 1, R>(M, T, Cf, A, 0);
-        } else {
-            tail_cycle<OP, NL, LV + 1, R>(M, T, Cf, A, 0);
-        }
-        const TailLv<R> &Tf = T[LV], &Tc = T[LV + 1];
-        const int nfine = 1 << (3 * Tf.L.logn);
-        for (int t = threadIdx.x; t < nfine; t += TAIL_THREADS)
-            dev_prolong<R>(Tf.L.u0, Tf.L.u1, Tf.L.logn, Tc.L.u0, Tc.L.u1, Tc.ru0, Tc.ru1,
-                           (size_t)t);
-        __syncthreads();
-        tail_sweeps<OP, R>(M, Tf, Cf[LV], A.nu2);
+        const TailView<OP, NL, LV + 1, R> Tc(A, lds);
+        tail_sweeps<OP, LOGN, R>(M, T.L, T.cf, A.nu1);
+        tail_restrict<OP, LOGN, R>(M, T.L, T.cf, Tc.L, Tc.cf, Tc.ru0, Tc.ru1,
+                                   reinterpret_cast<double *>(lds + tail_offset<OP>(NL, NL)));
+        // F: a coarse F-cycle, then a coarse V-cycle; W: two coarse W-cycles
+        const int visits = type == 0 ? 1 : 2;
+#pragma unroll 1
+        for (int v = 0; v < visits; ++v)
+            tail_cycle<OP, NL, LV + 1, R>(M, A, lds, type == 1 && v == 1 ? 0 : type);
+        tail_prolong<LOGN, R>(T.L.u0, Tc.L.u0, Tc.L.u1, Tc.ru0, Tc.ru1,
+                              reinterpret_cast<double *>(lds + tail_offset<OP>(NL, NL)));
+        tail_sweeps<OP, LOGN, R>(M, T.L, T.cf, A.nu2);
     }
-}
-
-template <typename R>
-__device__ __forceinline__ void lds_copy(R *dst, const R *src, int n) {
-    for (int t = threadIdx.x; t < n; t += TAIL_THREADS) dst[t] = src[t];
 }
 
 // The tail levels live in LDS for the whole sub-cycle: their fields are
@@ -658,42 +890,29 @@ template <int OP, int NL, typename R>
 __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Mod M, TailArgs<R> A) {
     extern __shared__ double lds_raw[];
     R *lds = reinterpret_cast<R *>(lds_raw);
-    TailLv<R> T[NL];
-    Coefs Cf[NL];
-    R *p = lds;
-#pragma unroll
-    for (int q = 0; q < NL; ++q) {
-        const TailLv<R> &G = A.lv[q];
-        const int half = 1 << (3 * G.L.logn - 1);
-        T[q] = G;
-        Cf[q] = A.cf[q];
-        R *u0 = p, *u1 = p + half, *d0 = p + 2 * half, *d1 = p + 3 * half;
-        R *f0 = p + 4 * half, *f1 = p + 5 * half;
-        p += 6 * half;
-        T[q].L.u0 = u0;
-        T[q].L.u1 = u1;
-        T[q].L.d0 = d0;
-        T[q].L.d1 = d1;
-        T[q].L.f0 = f0;
-        T[q].L.f1 = f1;
-        lds_copy<R>(d0, G.L.d0, half);
-        lds_copy<R>(d1, G.L.d1, half);
-        if (q == 0) {
-            lds_copy<R>(u0, G.L.u0, half);
-            lds_copy<R>(u1, G.L.u1, half);
-            lds_copy<R>(f0, G.L.f0, half);
-            lds_copy<R>(f1, G.L.f1, half);
-        } else {
-            T[q].ru0 = p;
-            T[q].ru1 = p + half;
-            p += 2 * half;
-        }
+    const TailView<OP, NL, 0, R> T(A, lds);
+    {
+        const TailView<OP, NL, (NL > 1 ? 1 : 0), R> T1(A, lds);
+        const TailView<OP, NL, (NL > 2 ? 2 : 0), R> T2(A, lds);
+        typename decltype(T)::In in0;
+        typename decltype(T1)::In in1;
+        typename decltype(T2)::In in2;
+        T.fetch(A, in0);
+        if constexpr (NL > 1) T1.fetch(A, in1);
+        if constexpr (NL > 2) T2.fetch(A, in2);
+        T.store(in0);
+        if constexpr (NL > 1) T1.store(in1);
+        if constexpr (NL > 2) T2.store(in2);
     }
     __syncthreads();
-    tail_cycle<OP, NL, 0, R>(M, T, Cf, A, A.cycle);
-    const int half0 = 1 << (3 * A.lv[0].L.logn - 1);
-    lds_copy<R>(A.lv[0].L.u0, T[0].L.u0, half0);
-    lds_copy<R>(A.lv[0].L.u1, T[0].L.u1, half0);
+    tail_cycle<OP, NL, 0, R>(M, A, lds, A.cycle);
+    // u0 and u1 lie one after the other in LDS
+    constexpr int half0 = 1 << (3 * (1 + NL) - 1);
+    for (int t = threadIdx.x; t < half0; t += TAIL_THREADS) {
+        const R a = T.L.u0[t], b = T.L.u1[t];
+        A.lv[0].L.u0[t] = a;
+        A.lv[0].L.u1[t] = b;
+    }
 }
 
 }  // namespace mgk
