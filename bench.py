@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0
 SWEEP_BYTES_PER_CELL = 24
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pass_dgp_512_traffic.json")
 KERNEL_SOURCES = ["paper_2110_00566_amd/csrc/mg_device.h", "paper_2110_00566_amd/csrc/mg_kernels.h",
-                  "paper_2110_00566_amd/csrc/mg_tiled.h", "paper_2110_00566_amd/csrc/mg_sweep.h"]
+                  "paper_2110_00566_amd/csrc/mg_tiled.h", "paper_2110_00566_amd/csrc/mg_sweep.h", "paper_2110_00566_amd/csrc/mg_small.h"]
 
 
 def kernel_hash() -> str:

@@ -24,6 +24,7 @@
 #include "mg_adj_tiled.h"
 #include "mg_adjoint.h"
 #include "mg_dc.h"
+#include "mg_small.h"
 #include "mg_sweep.h"
 
 using namespace mgk;
@@ -76,7 +77,7 @@ struct HLevel {
     size_t half = 0;
     R *u[2] = {nullptr, nullptr};
     R *spare = nullptr;
-    R *spare2 = nullptr;   // second output of the fused prolongation + pass (tiled levels)
+    R *spare2 = nullptr;   // second output of the kernels that write both colours
     R *d[2] = {nullptr, nullptr};
     R *f[2] = {nullptr, nullptr};
     R *ru[2] = {nullptr, nullptr};
@@ -190,7 +191,7 @@ void layout_hier(Hier<R> &Hh, Carve &cv, int n, bool adjoint, bool sym_coefs,
         H.u[0] = cv.take<R>(H.half);
         H.u[1] = cv.take<R>(H.half);
         H.spare = cv.take<R>(H.half);
-        if (!adjoint && m >= 128) H.spare2 = cv.take<R>(H.half);
+        if (!adjoint && (m >= 32 || L == 0)) H.spare2 = cv.take<R>(H.half);
         H.d[0] = cv.take<R>(H.half);
         H.d[1] = cv.take<R>(H.half);
         if (L > 0 || adjoint || dc_fine) {
@@ -618,6 +619,47 @@ struct Solver {
         }
     }
 
+    // Untiled levels outside the tail: fused kernels of mg_small.h (not for
+    // the finest level in profile mode, which times its colour passes).
+    bool small_level(int l) const {
+        return tiled_op(OP) && Hh.lv[l].spare2 && !tiled_level(Hh.lv[l].n) && !(C.profile && l == 0);
+    }
+    void small_down(int l) {
+        HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
+        const unsigned nb = 1u << (3 * (H.logn - 3));
+        if (l == 0) {
+            k_small_down<fwd_op(OP), true, R><<<nb, SMT, 0, C.st>>>(
+                C.M, view(H, false), H.spare, H.spare2, C.scal + S_MU, Hc.ru[0], Hc.ru[1],
+                (R *)Hc.f[0], (R *)Hc.f[1], C.partials, C.clamp);
+            // reduced by the launch that follows (coarse source or tail)
+            const double n = H.n;
+            pend = {C.partials, nb, n * n * n, C.scal, nullptr, 0};
+            pend.host = C.next_host(pend.seq);
+        } else {
+            k_small_down<fwd_op(OP), false, R><<<nb, SMT, 0, C.st>>>(
+                C.M, view(H, true), H.spare, H.spare2, nullptr, Hc.ru[0], Hc.ru[1], (R *)Hc.f[0],
+                (R *)Hc.f[1], C.partials, C.clamp);
+        }
+        std::swap(H.u[0], H.spare);
+        std::swap(H.u[1], H.spare2);
+    }
+    void small_up(int l) {
+        HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
+        const unsigned nb = 1u << (3 * (H.logn - 3));
+        k_small_up<fwd_op(OP), R><<<nb, SMT, 0, C.st>>>(
+            C.M, view(H, l > 0), H.spare, H.spare2, Hc.u[0], Hc.u[1], Hc.ru[0], Hc.ru[1],
+            l == 0 ? C.scal + S_MU : nullptr, C.clamp);
+        std::swap(H.u[0], H.spare);
+        std::swap(H.u[1], H.spare2);
+    }
+
+    Pending pend{};
+    Pending take_pending() {
+        const Pending p = pend;
+        pend = Pending{};
+        return p;
+    }
+
     // reduce the finest residual's nb block sums (k_finalize mode 0, 2 or 5)
     void finalize(unsigned nb, int mode) {
         const double n = Hh.lv[0].n;
@@ -680,7 +722,11 @@ struct Solver {
         }
     }
 
+    // The tail forms its first level's source itself in V-cycles (each source
+    // is used once there): no launch here.
+    bool source_in_tail(int lc) const { return !ADJ && C.cycle == 0 && lc == tail_start(); }
     void coarse_source(int lc) {
+        if (source_in_tail(lc)) return;
         HLevel<R> &Hc = Hh.lv[lc];
         LvlT<R> L = view(Hc, false);
         L.u0 = Hc.ru[0];
@@ -702,7 +748,7 @@ struct Solver {
                 C.M, L, Hc.f[0], Hc.f[1], Hc.u[0], Hc.u[1], shift, G);
         } else {
             k_coarse_source<OP, R><<<nblocks(2 * Hc.half), TPB, 0, C.st>>>(
-                C.M, L, coefs(Hc), Hc.f[0], Hc.f[1], Hc.u[0], Hc.u[1], shift);
+                C.M, L, coefs(Hc), Hc.f[0], Hc.f[1], Hc.u[0], Hc.u[1], shift, take_pending());
         }
     }
 
@@ -725,13 +771,13 @@ struct Solver {
     template <int NL>
     void launch_tail(const TailArgs<R> &A) {
         constexpr int lds = tail_lds_bytes<OP, R>(NL);
-        static_assert(lds <= 160 * 1024, "tail exceeds the LDS of a CU");
+        static_assert(lds + 512 <= 160 * 1024, "tail exceeds the LDS of a CU");
         // once per instantiation and process (thread-safe); a failure stays
         // in the HIP error state and is reported with the solve's launches
         static std::once_flag once;
         std::call_once(once, [] {
             (void)hipFuncSetAttribute((const void *)k_tail<OP, NL, R>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         });
         k_tail<OP, NL, R><<<1, TAIL_THREADS, lds, C.st>>>(C.M, A);
     }
@@ -745,6 +791,9 @@ struct Solver {
         A.nu2 = C.nu2;
         A.nuc = C.nuc;
         A.cycle = type;
+        A.source = source_in_tail(l);
+        A.shift = (A.source && l == 1 && OP != OP_ADJ) ? C.scal + S_SHIFT : nullptr;
+        A.pend = take_pending();
         for (int q = 0; q < A.nlev; ++q) {
             HLevel<R> &H = Hh.lv[l + q];
             A.lv[q].L = view(H, true);
@@ -795,8 +844,13 @@ struct Solver {
             segment(l, e0, mark());
             return;
         }
-        for (int s = 0; s < C.nu1; ++s) sweep(l);
-        resid_restrict(l);
+        if (C.nu1 >= 1 && small_level(l)) {
+            for (int s = 1; s < C.nu1; ++s) sweep(l);
+            small_down(l);   // the last pre-sweep with the residual
+        } else {
+            for (int s = 0; s < C.nu1; ++s) sweep(l);
+            resid_restrict(l);
+        }
         coarse_source(l + 1);
         segment(l, e0, mark());
         if (type == 2) {
@@ -811,6 +865,9 @@ struct Solver {
         const int e2 = mark();
         if (C.nu2 >= 1 && fused_sweep(l)) {
             launch_sweep<true>(l);   // the first post-sweep, prolongation included
+            for (int s = 1; s < C.nu2; ++s) sweep(l);
+        } else if (C.nu2 >= 1 && small_level(l)) {
+            small_up(l);
             for (int s = 1; s < C.nu2; ++s) sweep(l);
         } else {
             prolong(l);
@@ -1419,9 +1476,9 @@ mg_status common_checks(const mg_opts *o, const void *delta, const void *phi, vo
 }
 
 // Workspace of mg_solve_dgp_noalloc: enough for any precision at n <= 128
-// (mg_workspace_bytes(128, MG_MIXED, MG_MODEL_DGP, 0) is 87.6 MiB).
+// (mg_workspace_bytes(128, MG_MIXED, MG_MODEL_DGP, 0) is 89.3 MiB).
 constexpr int NOALLOC_MAX_N = 128;
-constexpr size_t NOALLOC_BYTES = (size_t)88 << 20;
+constexpr size_t NOALLOC_BYTES = (size_t)90 << 20;
 
 }  // namespace
 
@@ -1513,7 +1570,7 @@ mg_status mg_solve_dgp_noalloc(const mg_opts *opts, const mg_dgp_params *par,
     if (rc != MG_OK) return rc;
     if (opts->n > NOALLOC_MAX_N)
         return fail(MG_ERR_ARG, "mg_solve_dgp_noalloc: opts.n must be <= 128 (its static "
-                                "workspace holds 88 MiB); use mg_solve_dgp for larger meshes");
+                                "workspace holds 90 MiB); use mg_solve_dgp for larger meshes");
     if (opts->profile) return fail(MG_ERR_ARG, "mg_solve_dgp_noalloc: profile must be 0");
     if (!delta || !phi) return fail(MG_ERR_ARG, "delta and phi must be device pointers");
     if (!stats) return fail(MG_ERR_ARG, "stats is NULL");

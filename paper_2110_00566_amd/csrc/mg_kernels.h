@@ -148,8 +148,9 @@ __global__ __launch_bounds__(TPB) void k_pass(Mod M, LvlT<R> L, Coefs Cf, int c,
 }
 
 // Deterministic block sum of two values into partials[2*blk .. 2*blk+1].
+template <int NT = TPB>
 __device__ __forceinline__ void block_sum2(double a, double b, double *partials, size_t blk) {
-    __shared__ double sa[TPB / 64], sb[TPB / 64];
+    __shared__ double sa[NT / 64], sb[NT / 64];
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_down(a, off, 64);
         b += __shfl_down(b, off, 64);
@@ -162,7 +163,7 @@ __device__ __forceinline__ void block_sum2(double a, double b, double *partials,
     __syncthreads();
     if (threadIdx.x == 0) {
         double x = 0.0, y = 0.0;
-        for (int q = 0; q < TPB / 64; ++q) {
+        for (int q = 0; q < NT / 64; ++q) {
             x += sa[q];
             y += sb[q];
         }
@@ -256,8 +257,8 @@ __global__ __launch_bounds__(64) void k_mu_estimate(Mod M, LvlT<R> L, Coefs Cf, 
 // the restricted residual; the coarse unknown starts from R u.
 template <int OP, typename R>
 __device__ __forceinline__ void dev_coarse_source(const Mod &M, const LvlT<R> &Lc, const Coefs &Cf,
-                                                  R *s0, R *s1, R *u0, R *u1, const double *shift,
-                                                  int c, size_t tt) {
+                                                  R *s0, R *s1, R *u0, R *u1, double shift, int c,
+                                                  size_t tt) {
     const int m = (int)(tt & ((1u << Lc.lognh) - 1));
     const int j = (int)((tt >> Lc.lognh) & (Lc.n - 1));
     const int k = (int)(tt >> (Lc.lognh + Lc.logn));
@@ -266,19 +267,9 @@ __device__ __forceinline__ void dev_coarse_source(const Mod &M, const LvlT<R> &L
     const R ru = (c ? Lc.u1 : Lc.u0)[tt];
     if constexpr (OP == OP_NEWTON) term = newton_term(M, term, (faces - 6.0 * (double)ru) / Lc.h2);
     R *S = c ? s1 : s0;
-    const double rd = (double)S[tt] - (shift ? *shift : 0.0);
+    const double rd = (double)S[tt] - shift;
     S[tt] = (R)((faces - 6.0 * (double)ru) / Lc.h2 - term - rd);
     (c ? u1 : u0)[tt] = ru;
-}
-
-template <int OP, typename R>
-__global__ __launch_bounds__(TPB) void k_coarse_source(Mod M, LvlT<R> Lc, Coefs Cf, R *s0, R *s1,
-                                                       R *u0, R *u1, const double *shift) {
-    const size_t t = xcd_block(blockIdx.x, gridDim.x) * TPB + threadIdx.x;
-    const size_t half = (size_t)1 << (3 * Lc.logn - 1);
-    if (t >= 2 * half) return;
-    const int c = t >= half;
-    dev_coarse_source<OP, R>(M, Lc, Cf, s0, s1, u0, u1, shift, c, t - (c ? half : 0));
 }
 
 // u_fine += P(uc - rc) with the cell-centred trilinear weights 27/9/3/1 (/64).
@@ -407,14 +398,15 @@ __global__ __launch_bounds__(TPB) void k_sum(const R *a0, const R *a1, size_t nh
 // host: pinned host memory (or null).  The residual's scalars are stored there
 // too, then seq into host[S_NSCAL - 1]: the host waits for that number, with
 // no copy or event on the stream (they cost 14 us per cycle of a 32^3 solve).
-__global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_t nblocks,
-                                                   double ncells, double *scal, int mode,
-                                                   double kappa, int colour = 0,
-                                                   double *host = nullptr,
-                                                   unsigned long long seq = 0) {
-    __shared__ double sa[16], sb[16];
+
+// Sums of the nblocks pairs of block sums, by NT threads of a block (all call
+// it); the result is valid in thread 0.
+template <int NT>
+__device__ __forceinline__ void sum_partials(const double *partials, size_t nblocks, double &x,
+                                             double &y) {
+    __shared__ double sa[NT / 64], sb[NT / 64];
     double a = 0.0, b = 0.0;
-    for (size_t q = threadIdx.x; q < nblocks; q += 1024) {
+    for (size_t q = threadIdx.x; q < nblocks; q += NT) {
         a += partials[2 * q];
         b += partials[2 * q + 1];
     }
@@ -427,58 +419,89 @@ __global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_
         sb[threadIdx.x >> 6] = b;
     }
     __syncthreads();
+    x = y = 0.0;
     if (threadIdx.x == 0) {
-        double x = 0.0, y = 0.0;
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < NT / 64; ++q) {
             x += sa[q];
             y += sb[q];
         }
-        const double mean = x / ncells, msq = y / ncells;
-        if (mode == 0) {
-            const double mu = scal[S_MU] + mean;
-            scal[S_MU] = mu;
-            scal[S_SHIFT] = mean;
-            double v = msq - mean * mean;
-            v = v < 0.0 ? 0.0 : v;   // keeps NaN
-            scal[S_EPS2] = v;
-            if (host) {
-                host[S_MU] = mu;
-                host[S_EPS2] = v;
-            }
-        } else if (mode == 1) {
-            scal[S_MEAN] = mean;
+    }
+}
+
+// Scalars of a finest residual from its sums x (of d) and y (of d^2): modes 0,
+// 2 and 5 of k_finalize (one thread).
+__device__ __forceinline__ void residual_scalars(double x, double y, double ncells, double *scal,
+                                                 int mode, double kappa, double *host,
+                                                 unsigned long long seq) {
+    const double mean = x / ncells, msq = y / ncells;
+    const int imu = mode == 5 ? S_MU64 : S_MU, ieps = mode == 5 ? S_EPS64 : S_EPS2;
+    double v, mu = 0.0;
+    if (mode == 2) {
+        const double km = kappa * scal[S_MEAN];
+        scal[S_SHIFT] = 0.0;
+        v = msq - 2.0 * km * mean + km * km;
+    } else {
+        mu = scal[imu] + mean;
+        scal[imu] = mu;
+        if (mode == 0) scal[S_SHIFT] = mean;
+        v = msq - mean * mean;
+    }
+    v = v < 0.0 ? 0.0 : v;   // keeps NaN
+    scal[ieps] = v;
+    if (host) {
+        host[imu] = mu;
+        host[ieps] = v;
+        __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + S_NSCAL - 1, seq,
+                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_finalize(const double *partials, size_t nblocks,
+                                                   double ncells, double *scal, int mode,
+                                                   double kappa, int colour = 0,
+                                                   double *host = nullptr,
+                                                   unsigned long long seq = 0) {
+    double x, y;
+    sum_partials<1024>(partials, nblocks, x, y);
+    if (threadIdx.x == 0) {
+        if (mode == 1) {
+            scal[S_MEAN] = x / ncells;
         } else if (mode == 3) {
             scal[S_CSUM0 + colour] = x;
             scal[S_MEAN] = (scal[S_CSUM0] + scal[S_CSUM1]) / ncells;
-        } else if (mode == 5) {
-            const double mu = scal[S_MU64] + mean;
-            scal[S_MU64] = mu;
-            double v = msq - mean * mean;
-            v = v < 0.0 ? 0.0 : v;   // keeps NaN
-            scal[S_EPS64] = v;
-            if (host) {
-                host[S_MU64] = mu;
-                host[S_EPS64] = v;
-            }
         } else if (mode == 4) {
             scal[S_CSUM0] = x;
             scal[S_CSUM1] = y;
             scal[S_MEAN] = (x + y) / ncells;
         } else {
-            const double km = kappa * scal[S_MEAN];
-            scal[S_SHIFT] = 0.0;
-            double v = msq - 2.0 * km * mean + km * km;
-            v = v < 0.0 ? 0.0 : v;   // keeps NaN
-            scal[S_EPS2] = v;
-            if (host) {
-                host[S_MU] = 0.0;
-                host[S_EPS2] = v;
-            }
+            residual_scalars(x, y, ncells, scal, mode, kappa, host, seq);
         }
-        if (host)
-            __hip_atomic_store(reinterpret_cast<unsigned long long *>(host) + S_NSCAL - 1, seq,
-                               __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
+}
+
+// A finest residual's reduction carried into the next launch (the coarse
+// source or the tail), which then needs no k_finalize before it (mode 0, up to
+// 512 block sums: finest levels <= 64^3).  Every block sums the partials,
+// block 0 stores the scalars.
+struct Pending {
+    const double *partials;   // null: the scalars are stored already
+    unsigned nb;
+    double ncells;
+    double *scal, *host;
+    unsigned long long seq;
+};
+// The shift of the coarse source (S_SHIFT); every thread of the block calls it.
+template <int NT>
+__device__ __forceinline__ double pending_shift(const Pending &P, bool store) {
+    __shared__ double shift;
+    double x, y;
+    sum_partials<NT>(P.partials, P.nb, x, y);
+    if (threadIdx.x == 0) {
+        shift = x / P.ncells;
+        if (store) residual_scalars(x, y, P.ncells, P.scal, 0, 0.0, P.host, P.seq);
+    }
+    __syncthreads();
+    return shift;
 }
 
 __global__ void k_fill(double *a, size_t n, double v) {
@@ -512,6 +535,18 @@ __global__ __launch_bounds__(TPB) void k_residual(Mod M, Lvl L, Coefs Cf, const 
                       - rhs_at<double, double>(L, c, tt, fptr, fscale);
 }
 
+template <int OP, typename R>
+__global__ __launch_bounds__(TPB) void k_coarse_source(Mod M, LvlT<R> Lc, Coefs Cf, R *s0, R *s1,
+                                                       R *u0, R *u1, const double *shift,
+                                                       Pending P) {
+    const size_t blk = xcd_block(blockIdx.x, gridDim.x), t = blk * TPB + threadIdx.x;
+    const double sh = P.partials ? pending_shift<TPB>(P, blk == 0) : shift ? *shift : 0.0;
+    const size_t half = (size_t)1 << (3 * Lc.logn - 1);
+    if (t >= 2 * half) return;
+    const int c = t >= half;
+    dev_coarse_source<OP, R>(M, Lc, Cf, s0, s1, u0, u1, sh, c, t - (c ? half : 0));
+}
+
 // ---------------------------------------------------------------- coarse tail
 // All levels from 16^3 down to 4^3 in one workgroup: the sub-cycle (smoothing,
 // residual + restriction, coarse source, recursion, prolongation) runs with
@@ -532,13 +567,18 @@ constexpr int TAIL_MAX_LEVELS = 3;
 template <typename R>
 struct TailLv {
     LvlT<R> L;      // u, d and f (the FAS source, workspace: written by the tail)
-    R *ru0, *ru1;   // R u of the finer level (unused on the first tail level)
+    R *ru0, *ru1;   // R u of the finer level
 };
 
 template <typename R>
 struct TailArgs {
     int nlev, nu1, nu2, nuc;
     int cycle;   // 0 V, 1 F, 2 W
+    // the first level's coarse source is formed here (V-cycles, whose tail
+    // runs once per source): f then holds R d and u starts from R u
+    bool source;
+    const double *shift;   // of that source (null: 0), or pending
+    Pending pend;
     TailLv<R> lv[TAIL_MAX_LEVELS];
     Coefs cf[TAIL_MAX_LEVELS];
 };
@@ -699,7 +739,7 @@ __device__ __forceinline__ void tail_restrict(const Mod &M, const LvlT<R> &L, co
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int tid = tail_tid();
-#pragma unroll 1
+#pragma unroll
         for (int q = 0; q < CNT; ++q) {
             const int t = tid + q * TAIL_THREADS;
             if (HALF % TAIL_THREADS == 0 || t < HALF) {
@@ -740,7 +780,7 @@ __device__ __forceinline__ void tail_restrict(const Mod &M, const LvlT<R> &L, co
         Lr.u1 = ru1;
         constexpr int HC = NC3 / 2;
         auto source = [&](int c, int tt) __attribute__((always_inline)) {
-            dev_coarse_source<OP, R>(M, Lr, Cc, S0, S1, Lc.u0, Lc.u1, nullptr, c, (size_t)tt);
+            dev_coarse_source<OP, R>(M, Lr, Cc, S0, S1, Lc.u0, Lc.u1, 0.0, c, (size_t)tt);
         };
         if constexpr (OP == OP_ADJ) {   // the coefficient pointers need a constant colour
             if (t < HC)
@@ -832,7 +872,11 @@ struct TailView {
     static __device__ __forceinline__ const R *source(const TailArgs<R> &A, int i) {
         const LvlT<R> &G = A.lv[LV].L;
         constexpr int NF = LV == 0 ? 4 : 0;
-        if (i < NF) return i == 0 ? G.u0 : i == 1 ? G.u1 : i == 2 ? G.f0 : G.f1;
+        if (i < NF)
+            return i == 0   ? (A.source ? A.lv[LV].ru0 : G.u0)
+                   : i == 1 ? (A.source ? A.lv[LV].ru1 : G.u1)
+                   : i == 2 ? G.f0
+                            : G.f1;
         if (OP != OP_ADJ) return i == NF ? G.d0 : G.d1;
         return (const R *)A.cf[LV].c[(i - NF) >> 1][(i - NF) & 1];
     }
@@ -905,6 +949,24 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail(Mod M, TailArgs<R> A) {
         if constexpr (NL > 2) T2.store(in2);
     }
     __syncthreads();
+    if (A.source) {
+        const double shift = A.pend.partials ? pending_shift<TAIL_THREADS>(A.pend, true)
+                             : A.shift       ? *A.shift
+                                             : 0.0;
+        constexpr int HALF = decltype(T)::HALF, CNT = decltype(T)::CNT;
+        const int tid = tail_tid();
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int q = 0; q < CNT; ++q) {
+                const int t = tid + q * TAIL_THREADS;
+                if (HALF % TAIL_THREADS == 0 || t < HALF)
+                    dev_coarse_source<OP, R>(M, T.L, T.cf, T.f0, T.f1, T.L.u0, T.L.u1, shift, c,
+                                             (size_t)t);
+            }
+        }
+        __syncthreads();
+    }
     tail_cycle<OP, NL, 0, R>(M, A, lds, A.cycle);
     // u0 and u1 lie one after the other in LDS
     constexpr int half0 = 1 << (3 * (1 + NL) - 1);
