@@ -1,6 +1,7 @@
 // LDS-tiled kernels of the adjoint solve (J^T mu = f by FAS-free linear
-// multigrid with the Jacobian coefficients stored per level), for levels with
-// at least 128 cells per side.
+// multigrid with the Jacobian coefficients stored per level: Kmouflage and
+// Poisson; k_adj_dgp rebuilds the nDGP ones), for levels with at least 128
+// cells per side.
 //
 // (J^T mu)_p = lap(mu)_p - G_p with G_p = sum over the 18 neighbours q of p of
 // dK_q/dphi_p mu_q (the diagonal of J^T is exactly -6/h^2: no model term
@@ -19,8 +20,8 @@
 // in-plane terms) and k'+1 (their -z terms); a thread keeps these partial
 // sums for its own column in registers, so a cell is complete once the plane
 // above it has been staged.  The z-face products of the thread's own column
-// come from direct loads.  32 KB of LDS (nDGP, Poisson), 42 KB (Kmouflage,
-// whose x+/x- face coefficients differ).
+// come from direct loads.  5 KB of LDS (Poisson), 42 KB (Kmouflage, whose
+// x+/x- face coefficients differ).
 //
 // One kernel, three modes, one colour c per launch:
 //   PASS   mu_c <- (faces - h^2 (G + f_c + fs)) / 6 into a fresh array;
@@ -40,9 +41,9 @@ enum { ADJ_PASS = 0, ADJ_RESID = 1, ADJ_CSRC = 2 };
 
 struct AdjLevel {
     const double *u0, *u1;       // mu (CSRC: R mu of the finer level)
-    const double *c[9][2];       // coefficient arrays (minus faces alias plus for nDGP/Poisson)
-    const double *lin[2];        // RC: linearisation point phi of the level
-    const double *kp[2];         // RC: dK/dSigma at every cell
+    const double *c[9][2];       // coefficient arrays (Kmouflage)
+    const double *lin[2];        // nDGP: linearisation point phi of the level
+    const double *kp[2];         // nDGP: dK/dSigma at every cell (no c[] then)
     const double *f0, *f1;       // right-hand side, never null (CSRC: R r, overwritten by S)
     int n, logn, lognh;
     double h2;
@@ -174,40 +175,20 @@ __device__ __forceinline__ void block_sum2_nt(double a, double b, double *partia
     }
 }
 
-// SYM: the x+ and x- (y, z) face coefficients are one array (nDGP, Poisson);
 // COEF: the model has a non-Laplacian term (not Poisson).  REDUCE: block sums
 // into partials[2 blk ..] (PASS: the new values; RESID: r and r^2).
-//
-// RC (nDGP): the products are rebuilt from the linearisation point instead
-// of read from coefficient arrays.  With F' = dK/dSigma of a cell (the one
-// array kept per level), the face coefficient of a face-colour cell is
-// 2 F' (2A_x - A_y - A_z)/(3h^4) and the edge coefficient of a target-colour
-// cell 2 F' N_xy/(8h^4) (y, z alike, as in k_adj_coefs); both read only the
-// target colour's phi (the face neighbours of a face-colour cell and the
-// edge neighbours of a target-colour cell have the target colour).  phi_c is
-// staged on the tile with a 2-cell halo (68 x 12 values per plane) in a ring
-// of 4 planes, two planes ahead of the products, so a plane's products see
-// phi at k - 1, k and k + 1.  Per cell and pass: mu of both colours, phi of
-// the target colour, F' of both colours, f and the new value (28 B against
-// 40 B with the stored coefficients).
-template <int NT, bool SYM, bool COEF, int MODE, bool REDUCE, bool RC = false>
-__global__ __launch_bounds__(NT)
-__attribute__((amdgpu_waves_per_eu(RC ? 4 : 1))) void k_adj_tiled(AdjLevel L, int c, double *out, double *out2,
-                                                   const double *fptr,
-                                                   double fscale, double *ru0, double *ru1,
-                                                   double *rd0, double *rd1, double *partials,
-                                                   TileGeom G) {
-    constexpr int NF = SYM ? 2 : 4;   // staged in-plane face product arrays
+template <int NT, bool COEF, int MODE, bool REDUCE>
+__global__ __launch_bounds__(NT) void k_adj_tiled(AdjLevel L, int c, double *out, double *out2,
+                                                  const double *fptr, double fscale,
+                                                  double *ru0, double *ru1, double *rd0,
+                                                  double *rd1, double *partials, TileGeom G) {
+    constexpr int NF = 4;             // staged in-plane face product arrays
     constexpr int W = NT / 64;        // waves = rows per row group
     constexpr int RPT = TY / W;       // rows per thread
     __shared__ __align__(16) double sM[TSLOT];
     __shared__ __align__(16) double sF[COEF ? NF : 1][TSLOT];
     __shared__ __align__(16) double sE[COEF ? 3 : 1][TSLOT];
     __shared__ double sX[MODE == ADJ_RESID ? 2 * RPT : 1][MODE == ADJ_RESID ? NT : 1];
-    constexpr int PW = TX + 4, PH = TY + 4;        // RC: phi_c plane with a 2-cell halo
-    constexpr int PSLOT = PW * PH, PNV = PH * (PW / 2);
-    static_assert(!RC || (SYM && COEF && NT >= PNV), "RC: nDGP, one phi vector per thread");
-    __shared__ __align__(16) double sP[RC ? 4 : 1][RC ? PSLOT : 2];
     const size_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int bx = (int)(blk % G.ntx);
     const int by = (int)((blk / G.ntx) % G.nty);
@@ -228,102 +209,28 @@ __attribute__((amdgpu_waves_per_eu(RC ? 4 : 1))) void k_adj_tiled(AdjLevel L, in
     for (int h = 0; h < RPT; ++h) coff[h] = cell_off<double>(j0 + ty + W * h, m0 + tx, L.lognh);
 
     // staged raw values of the next plane
-    SReg<NT> rMo, rFx, rFy, rFx2, rFy2, rMc, rE6, rE7, rE8, rKo, rKc;
-    // RC: phi_c of a plane (vector tid of 408: row tid / 34, packed columns
-    // m0 - 2 + 2 (tid % 34) and the next), two planes ahead of the products
-    unsigned pg = 0;
-    int plds = 0;
-    if constexpr (RC) {
-        const int v = tid < PNV ? tid : 0;
-        const int r = v / (PW / 2), i = v - r * (PW / 2);
-        const unsigned jm = (1u << L.logn) - 1, mm = (1u << L.lognh) - 1;
-        pg = ((((unsigned)(j0 - 2 + r) & jm) << L.lognh) + ((unsigned)(m0 - 2 + 2 * i) & mm)) * 8u;
-        plds = r * PW + 2 * i;
-    }
-    const double *Pc = L.lin[c];
-    double2 rP = make_double2(0.0, 0.0);
-    auto pfetch = [&](int k) {
-        if (RC && tid < PNV)
-            rP = *reinterpret_cast<const double2 *>(
-                reinterpret_cast<const char *>(Pc) + plane_off<double>(k, L.logn, L.lognh) + pg);
-    };
-    auto pstore = [&](int k) {
-        if (RC && tid < PNV) *reinterpret_cast<double2 *>(sP[(k + 4) & 3] + plds) = rP;
-    };
+    SReg<NT> rMo, rFx, rFy, rFx2, rFy2, rMc, rE6, rE7, rE8;
     auto fetch = [&](int k) {
         const size_t pl = plane_off<double>(k, L.logn, L.lognh);
         rMo.load(Mo, pl, g, tid);
-        if constexpr (RC) {
-            rMc.load(Mc, pl, g, tid);
-            rKo.load(L.kp[o], pl, g, tid);
-            rKc.load(L.kp[c], pl, g, tid);
-            pfetch(k + 2);
-        } else if constexpr (COEF) {
+        if constexpr (COEF) {
             rFx.load(L.c[0][o], pl, g, tid);
             rFy.load(L.c[2][o], pl, g, tid);
-            if constexpr (!SYM) {
-                rFx2.load(L.c[1][o], pl, g, tid);
-                rFy2.load(L.c[3][o], pl, g, tid);
-            }
+            rFx2.load(L.c[1][o], pl, g, tid);
+            rFy2.load(L.c[3][o], pl, g, tid);
             rMc.load(Mc, pl, g, tid);
             rE6.load(L.c[6][c], pl, g, tid);
             rE7.load(L.c[7][c], pl, g, tid);
             rE8.load(L.c[8][c], pl, g, tid);
         }
     };
-    // RC: face sums of the face-colour cell and cross differences of the
-    // target-colour cell at staged position (r, ci) of plane kp (r: row
-    // j0 - 1 + r, ci: packed column m0 - 1 + ci) from the phi_c ring
-    auto faces_at = [&](int r, int ci, int kp, double &ax, double &ay, double &az) {
-        const int po = (o + j0 - 1 + r + kp) & 1;
-        const double *P0 = sP[(kp + 4) & 3], *Pm = sP[(kp + 3) & 3], *Pp = sP[(kp + 5) & 3];
-        const int r0 = (r + 1) * PW, rp = (r + 2) * PW, rm = r * PW, x0 = ci + 1;
-        ax = P0[r0 + x0 + po] + P0[r0 + ci + po];
-        ay = P0[rp + x0] + P0[rm + x0];
-        az = Pp[r0 + x0] + Pm[r0 + x0];
-    };
-    auto prod = [&](int r, int ci, int kp, int l, double mo, double ko, double mc, double kc) {
-        if constexpr (!RC) return;
-        double ax, ay, az;
-        faces_at(r, ci, kp, ax, ay, az);
-        const double w = 2.0 * ko * L.c3h4;
-        sF[0][1 + l] = w * (2.0 * ax - ay - az) * mo;
-        sF[COEF ? 1 : 0][1 + l] = w * (2.0 * ay - ax - az) * mo;
-        const int pc = (c + j0 - 1 + r + kp) & 1;
-        const double *P0 = sP[(kp + 4) & 3], *Pm = sP[(kp + 3) & 3], *Pp = sP[(kp + 5) & 3];
-        const int r0 = (r + 1) * PW, rp = (r + 2) * PW, rm = r * PW, x0 = ci + 1;
-        const int xp = x0 + pc, xm = ci + pc;
-        const double nxy = (P0[rp + xp] + P0[rm + xm]) - (P0[rm + xp] + P0[rp + xm]);
-        const double nxz = (Pp[r0 + xp] + Pm[r0 + xm]) - (Pm[r0 + xp] + Pp[r0 + xm]);
-        const double nyz = (Pp[rp + x0] + Pm[rm + x0]) - (Pm[rp + x0] + Pp[rm + x0]);
-        const double e = 2.0 * kc * L.c8h4;
-        sE[0][1 + l] = e * nxy * mc;
-        sE[COEF ? 1 : 0][1 + l] = e * nxz * mc;
-        sE[COEF ? 2 : 0][1 + l] = e * nyz * mc;
-    };
-    auto store = [&](int kp) {
+    auto store = [&]() {
         rMo.store(sM + 1, g, tid);
-        if constexpr (RC) {
-            pstore(kp + 2);
-            using SG = SGeom<NT>;
-            if (tid < SG::NV) {
-                const int r = tid >> 5, ci = 1 + 2 * (tid & 31);
-                prod(r, ci, kp, g.l0, rMo.a0.x, rKo.a0.x, rMc.a0.x, rKc.a0.x);
-                // residual and coarse source: one position at a time
-                // (interleaved, they spill); the pass is faster interleaved
-                if constexpr (MODE != ADJ_PASS) __builtin_amdgcn_sched_barrier(0);
-                prod(r, ci + 1, kp, g.l0 + 1, rMo.a0.y, rKo.a0.y, rMc.a0.y, rKc.a0.y);
-            } else if (tid < SG::H0 + 2 * TYH) {
-                const int hh = tid - SG::H0, r = hh >> 1, ci = (hh & 1) ? TXH - 1 : 0;
-                prod(r, ci, kp, g.l0, rMo.a0.x, rKo.a0.x, rMc.a0.x, rKc.a0.x);
-            }
-        } else if constexpr (COEF) {
+        if constexpr (COEF) {
             rFx.store_prod(sF[0] + 1, rMo, g, tid);
             rFy.store_prod(sF[1] + 1, rMo, g, tid);
-            if constexpr (!SYM) {
-                rFx2.store_prod(sF[NF - 2] + 1, rMo, g, tid);
-                rFy2.store_prod(sF[NF - 1] + 1, rMo, g, tid);
-            }
+            rFx2.store_prod(sF[NF - 2] + 1, rMo, g, tid);
+            rFy2.store_prod(sF[NF - 1] + 1, rMo, g, tid);
             rE6.store_prod(sE[0] + 1, rMc, g, tid);
             rE7.store_prod(sE[COEF ? 1 : 0] + 1, rMc, g, tid);
             rE8.store_prod(sE[COEF ? 2 : 0] + 1, rMc, g, tid);
@@ -337,11 +244,9 @@ __attribute__((amdgpu_waves_per_eu(RC ? 4 : 1))) void k_adj_tiled(AdjLevel L, in
         const size_t pl = plane_off<double>(k, L.logn, L.lognh);
 #pragma unroll
         for (int h = 0; h < RPT; ++h) {
-            if constexpr (RC) {
-                z4n[h] = ld(L.kp[o], pl, coff[h]);   // F' of the face-colour cell
-            } else if constexpr (COEF) {
+            if constexpr (COEF) {
                 z4n[h] = ld(L.c[4][o], pl, coff[h]);
-                z5n[h] = SYM ? z4n[h] : ld(L.c[5][o], pl, coff[h]);
+                z5n[h] = ld(L.c[5][o], pl, coff[h]);
             }
             // (also at the two planes outside the chunk, where they are unused:
             // plane_off wraps, so the loads stay inside the level)
@@ -385,28 +290,15 @@ __attribute__((amdgpu_waves_per_eu(RC ? 4 : 1))) void k_adj_tiled(AdjLevel L, in
         }
     };
 
-    if constexpr (RC) {   // phi_c planes k0 - 2 .. k0 (the products of k0 - 1 need them)
-        for (int kk = k0 - 2; kk <= k0; ++kk) {
-            pfetch(kk);
-            pstore(kk);
-        }
-    }
     fetch(k0 - 1);
     fetch_cells(k0 - 1);
-    if constexpr (RC) __syncthreads();
     for (int kp = k0 - 1; kp <= k1; ++kp) {
-        store(kp);
+        store();
         double z4[RPT], z5[RPT];
 #pragma unroll
         for (int h = 0; h < RPT; ++h) {
-            if constexpr (RC) {
-                double ax, ay, az;
-                faces_at(ty + W * h + 1, tx + 1, kp, ax, ay, az);
-                z4[h] = 2.0 * z4n[h] * L.c3h4 * (2.0 * az - ax - ay);
-            } else {
-                z4[h] = z4n[h];
-            }
-            z5[h] = SYM ? z4[h] : z5n[h];
+            z4[h] = z4n[h];
+            z5[h] = z5n[h];
             fp[h] = fc[h];
             up[h] = uc[h];
             fc[h] = fn[h];

@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "../../include/mgglam.h"
+#include "mg_adj_dgp.h"
 #include "mg_adj_tiled.h"
 #include "mg_adjoint.h"
 #include "mg_dc.h"
@@ -300,13 +301,13 @@ constexpr bool tiled_op(int OP) { return OP != OP_ADJ; }
 // planes each) keep at most 64: the 1024^3 residual + restriction took 4.43 ms
 // with 128 against 4.31 ms with 64.  The adjoint kernels, which stage four planes
 // before the first result, keep at least 4 (128^3 gradient 8.6 ms, 8.9 with 2).
-TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2) {
+TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2, int blocks = 2048) {
     TileGeom G;
     G.ntx = (n / 2) / TX;
     G.nty = n / TY;
     const long per = (long)G.ntx * G.nty;
     int kz = kzmax;
-    while (kz > kzmin && (long)planes * per / kz < 2048) kz >>= 1;
+    while (kz > kzmin && (long)planes * per / kz < blocks) kz >>= 1;
     while (planes % kz) kz >>= 1;
     G.kz = kz;
     return G;
@@ -369,12 +370,16 @@ unsigned launch_resid_restrict(const Mod &M, const LvlT<R> &L, const Coefs &Cf, 
     return nb;
 }
 
+// 4096 blocks: the 512^3 prolongation with colour sums took 539 us, with 2048
+// blocks 629 us.
+TileGeom prolong_geom(int n) { return tile_geom(n, n / 2, 64, 2, 4096); }
+
 template <typename R>
 void launch_prolong(R *f0, R *f1, int logn, const R *uc0, const R *uc1, const R *rc0,
                     const R *rc1, hipStream_t st) {
     const int n = 1 << logn;
     if (tiled_level(n)) {
-        const TileGeom G = tile_geom(n, n / 2, 64);
+        const TileGeom G = prolong_geom(n);
         k_prolong_tiled<R><<<tile_blocks(G, n / 2), TPB, 0, st>>>(f0, f1, logn, uc0, uc1, rc0, rc1,
                                                                  G);
     } else {
@@ -417,22 +422,21 @@ template <int MODE, bool REDUCE>
 unsigned launch_adj_tiled(int model, const AdjLevel &A, int c, double *out, double *out2,
                           const double *fptr, double fscale, double *ru0, double *ru1,
                           double *rd0, double *rd1, double *partials, hipStream_t st) {
+    if (model == MODEL_DGP) {   // coefficients rebuilt from dK/dSigma and phi
+        const TileGeom G = sweep_geom(A.n);
+        const unsigned nb = tile_blocks(G, A.n);
+        k_adj_dgp<MODE, REDUCE><<<nb, SNT, 0, st>>>(A, c, out, out2, fptr, fscale, ru0, ru1, rd0,
+                                                    rd1, partials, G);
+        return nb;
+    }
     const TileGeom G = tile_geom(A.n, A.n, 64, 4);
     const unsigned nb = tile_blocks(G, A.n);
-    switch (model) {
-        case MODEL_KMO:
-            k_adj_tiled<ADJ_NT, false, true, MODE, REDUCE><<<nb, ADJ_NT, 0, st>>>(
-                A, c, out, out2, fptr, fscale, ru0, ru1, rd0, rd1, partials, G);
-            break;
-        case MODEL_POISSON:
-            k_adj_tiled<ADJ_NT, true, false, MODE, REDUCE><<<nb, ADJ_NT, 0, st>>>(
-                A, c, out, out2, fptr, fscale, ru0, ru1, rd0, rd1, partials, G);
-            break;
-        default:   // nDGP: coefficients rebuilt from dK/dSigma and phi
-            k_adj_tiled<ADJ_NT, true, true, MODE, REDUCE, true><<<nb, ADJ_NT, 0, st>>>(
-                A, c, out, out2, fptr, fscale, ru0, ru1, rd0, rd1, partials, G);
-            break;
-    }
+    if (model == MODEL_KMO)
+        k_adj_tiled<ADJ_NT, true, MODE, REDUCE><<<nb, ADJ_NT, 0, st>>>(
+            A, c, out, out2, fptr, fscale, ru0, ru1, rd0, rd1, partials, G);
+    else
+        k_adj_tiled<ADJ_NT, false, MODE, REDUCE><<<nb, ADJ_NT, 0, st>>>(
+            A, c, out, out2, fptr, fscale, ru0, ru1, rd0, rd1, partials, G);
     return nb;
 }
 
@@ -756,7 +760,7 @@ struct Solver {
         HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
         if (l == 0 && adj_tiled(0)) {
             // the colour sums of the corrected finest field
-            const TileGeom G = tile_geom(H.n, H.n / 2, 64);
+            const TileGeom G = prolong_geom(H.n);
             const unsigned nb = tile_blocks(G, H.n / 2);
             k_prolong_tiled<R, true><<<nb, TPB, 0, C.st>>>(H.u[0], H.u[1], H.logn, Hc.u[0],
                                                           Hc.u[1], Hc.ru[0], Hc.ru[1], G,

@@ -46,6 +46,15 @@ struct LvlT {
 };
 using Lvl = LvlT<double>;
 
+// A value that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(x)));
+}
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+
 __device__ __forceinline__ size_t prow(int j, int k, int logn, int lognh) {
     return ((size_t)k << (logn + lognh)) + ((size_t)j << lognh);
 }
