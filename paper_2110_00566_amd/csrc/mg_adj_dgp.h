@@ -75,16 +75,16 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_adj_dgp(AdjLevel L, int c, double
     auto fetch = [&](int k) {
         const char *p = reinterpret_cast<const char *>(Pc) + plane_off<double>(k, L.logn, L.lognh) + S.g;
         if (w >= VW0)
-            S.a = *reinterpret_cast<const SweepStage<double>::Vec *>(p);
+            S.va[0] = *reinterpret_cast<const SweepStage<double>::Vec *>(p);
         else if (w == 0 && lane < 2 * SROWS)
-            S.a[0] = *reinterpret_cast<const double *>(p);
+            S.va[0][0] = *reinterpret_cast<const double *>(p);
     };
     auto store = [&](int k) {
         double *s = sP[k & 3] + 1;
         if (w >= VW0)
-            *reinterpret_cast<SweepStage<double>::Vec *>(s + S.l) = S.a;
+            *reinterpret_cast<SweepStage<double>::Vec *>(s + S.l) = S.va[0];
         else if (w == 0 && lane < 2 * SROWS)
-            s[S.l] = S.a[0];
+            s[S.l] = S.va[0][0];
     };
 
     // own column and the extra one of waves 0..2 (see k_sweep_tiled)

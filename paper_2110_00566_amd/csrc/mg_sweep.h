@@ -25,6 +25,13 @@
 // Step kp (after one barrier) reads plane kp, finishes the colour-0 cells of
 // plane kp - 1 and the colour-1 cells of plane kp - 3, writes the staged
 // values of plane kp + 1 and starts the loads of plane kp + 2.
+//
+// At 512^3 FP64 a sweep takes 610 us, 5.3 TB/s of its 24 B per cell (830 us as
+// two colour passes): HBM bounds it.  FP32, 410 us, is bound by instruction
+// issue: its vector instructions fill 80% of the cycles.  The prolongation adds
+// 115 us (190 us before a coarse plane's in-plane part was kept for the fine
+// planes that it serves).  Registers are what two blocks per CU leave short (128
+// a thread, 100 to 128 used): see the opaque copies and pins below.
 #pragma once
 #include <type_traits>
 #include "mg_tiled.h"
@@ -43,6 +50,12 @@ static_assert(SNT == 64 * TY, "one wave per tile row");
 constexpr int SCW = TX + 4, SCH = SROWS / 2 + 2, SCPLANE = SCW * SCH;
 static_assert(SCH * 64 == SNT, "one wave per coarse row");
 
+// Planes whose loads are in flight during a step.  Two for FP32: with one, the
+// two resident blocks of a CU have 20 KB of loads outstanding, too little for
+// the latency of HBM (FP64: 40 KB).
+template <typename R>
+constexpr int prefetch() { return sizeof(R) == 4 ? 2 : 1; }
+
 // Staging of a plane of both colours: 16-byte vectors of the 64 interior
 // columns by the last NV threads, the two halo columns by the first 24.
 template <typename R>
@@ -53,9 +66,10 @@ struct SweepStage {
     static constexpr int V0 = SNT - NV;             // first vector thread
     static_assert(V0 >= 64 && V0 % 64 == 0 && 2 * SROWS <= 64, "staging split");
     typedef R Vec __attribute__((ext_vector_type(VW)));
+    static constexpr int PF = prefetch<R>();
     unsigned g;   // byte offset inside a plane
     int l;        // value offset inside a plane view
-    Vec a, b;
+    Vec va[PF], vb[PF];   // planes in flight: plane k in k % PF
     __device__ __forceinline__ void init(int tid, int j0, int m0, int logn, int lognh) {
         const unsigned jm = (1u << logn) - 1, mm = (1u << lognh) - 1;
         int r, q;
@@ -74,7 +88,9 @@ struct SweepStage {
         g = ((((unsigned)(j0 - 2 + r) & jm) << lognh) + m) * (unsigned)sizeof(R);
         l = r * TXH + q;
     }
-    __device__ __forceinline__ void fetch(const R *A, const R *B, size_t pl, int w, int lane) {
+    __device__ __forceinline__ void fetch(const R *A, const R *B, size_t pl, int slot, int w,
+                                          int lane) {
+        Vec &a = va[slot % PF], &b = vb[slot % PF];
         const char *pa = reinterpret_cast<const char *>(A) + pl + g;
         const char *pb = reinterpret_cast<const char *>(B) + pl + g;
         if (w >= V0 / 64) {
@@ -86,43 +102,49 @@ struct SweepStage {
         }
     }
     // Add the prolonged coarse correction to the fetched values of a plane k
-    // (odd: k & 1).  eo, en: the coarse correction in the plane's own coarse
-    // plane and in its neighbour on the plane's side; ec, ed: offsets there of
-    // the own coarse row and of its neighbour on the row's side (ed > ec: the
-    // row is odd).  The 27/9/3/1 weights factor into 9, 3, 3, 1 in the plane
+    // (odd: k & 1).  The 27/9/3/1 weights factor into 9, 3, 3, 1 in the plane
     // and 3, 1 between the planes; FP32 rounds in this order in every kernel.
+    // A coarse plane's in-plane part (x: per value and x parity) serves four
+    // fine planes: it is formed when the first of them, an odd one, is staged
+    // and kept in registers (xo: the coarse plane below, xn: the newest).
+    R xo[VW][2], xn[VW][2];
+    // e: the coarse plane; ec, ed: offsets there of the own coarse row and of
+    // its neighbour on the row's side (ed > ec: the row is odd)
     template <int N>
-    __device__ __forceinline__ void correct(const R *eo, const R *en, int ec, int ed, bool odd) {
+    __device__ __forceinline__ void inplane(const R *e, int ec, int ed) {
         const R w9 = (R)(9.0 / 16.0), w3 = (R)(3.0 / 16.0), w1 = (R)(1.0 / 16.0);
-        const bool p0 = (ed > ec) != odd;   // x parity of the colour-0 values
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            R x[2][2];   // own and neighbouring plane, x parity
+            const R c = w9 * e[ec + i], d = e[ed + i];
+            xo[i][0] = xn[i][0];
+            xo[i][1] = xn[i][1];
+            xn[i][0] = fma(w1, e[ed + i - 1], fma(w3, d, fma(w3, e[ec + i - 1], c)));
+            xn[i][1] = fma(w1, e[ed + i + 1], fma(w3, d, fma(w3, e[ec + i + 1], c)));
+        }
+    }
+    __device__ __forceinline__ void inplane(const R *e, int ec, int ed, int w, int lane) {
+        if (w >= V0 / 64)
+            inplane<VW>(e, ec, ed);
+        else if (w == 0 && lane < 2 * SROWS)
+            inplane<1>(e, ec, ed);
+    }
+    __device__ __forceinline__ void correct(int ec, int ed, bool odd) {
+        Vec &a = va[odd % PF], &b = vb[odd % PF];
+        const bool p0 = (ed > ec) != odd;   // x parity of the colour-0 values
 #pragma unroll
-            for (int z = 0; z < 2; ++z) {
-                const R *e = z ? en : eo;
-                const R c = w9 * e[ec + i], d = e[ed + i];
-                x[z][0] = fma(w1, e[ed + i - 1], fma(w3, d, fma(w3, e[ec + i - 1], c)));
-                x[z][1] = fma(w1, e[ed + i + 1], fma(w3, d, fma(w3, e[ec + i + 1], c)));
-            }
+        for (int i = 0; i < VW; ++i) {
             R v[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q)
-                v[q] = odd ? fma((R)0.75, x[0][q], (R)0.25 * x[1][q])
-                           : fma((R)0.25, x[1][q], (R)0.75 * x[0][q]);
+                v[q] = odd ? fma((R)0.75, xo[i][q], (R)0.25 * xn[i][q])
+                           : fma((R)0.25, xo[i][q], (R)0.75 * xn[i][q]);
             a[i] += p0 ? v[1] : v[0];
             b[i] += p0 ? v[0] : v[1];
         }
     }
-    __device__ __forceinline__ void correct(const R *eo, const R *en, int ec, int ed, bool odd,
-                                            int w, int lane) {
-        if (w >= V0 / 64)
-            correct<VW>(eo, en, ec, ed, odd);
-        else if (w == 0 && lane < 2 * SROWS)
-            correct<1>(eo, en, ec, ed, odd);
-    }
     // sa, sb: the slots' plane views (slot base + 1)
-    __device__ __forceinline__ void store(R *sa, R *sb, int w, int lane) const {
+    __device__ __forceinline__ void store(R *sa, R *sb, int slot, int w, int lane) const {
+        const Vec &a = va[slot % PF], &b = vb[slot % PF];
         if (w >= V0 / 64) {
             if constexpr (sizeof(R) == 8) {
                 *reinterpret_cast<Vec *>(sa + l) = a;
@@ -230,8 +252,12 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     // ring of staged planes: slot k & 3 holds plane k of colours 0 and 1
     __shared__ __align__(16) R sS[4][2][SSLOT];
     __shared__ R sC[2][TPLANE];   // new colour-0 values, rows -1 .. TY
-    // ring of coarse planes (the correction): slot Z & 3
-    __shared__ R sE[PROLONG ? 4 : 1][PROLONG ? SCPLANE : 1];
+    // the coarse correction; CARRY: its in-plane part is kept in registers and
+    // one coarse plane is staged; FP64 Kmouflage and Newton have none to spare
+    // (Kmouflage spills, 125 -> 158 us at 256^3) and form it for every fine
+    // plane from a ring of coarse planes
+    constexpr bool CARRY = OP == OP_DGP || OP == OP_POISSON || sizeof(R) == 4;
+    __shared__ R sE[PROLONG && !CARRY ? 4 : 1][PROLONG ? SCPLANE : 1];
     const size_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int bx = (int)(blk % G.ntx);
     const int by = (int)((blk / G.ntx) % G.nty);
@@ -239,17 +265,20 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     const int m0 = bx * TX, j0 = by * TY, k0 = bz * G.kz, k1 = k0 + G.kz;   // kz is even
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const R fs = (R)(fptr ? fscale * (*fptr) : 0.0);
+    const R fs = uniform((R)(fptr ? fscale * (*fptr) : 0.0));
     SweepStage<R> S;
     S.init(tid, j0, m0, L.logn, L.lognh);
-    auto fetch = [&](int k) { S.fetch(L.u0, L.u1, plane_off<R>(k, L.logn, L.lognh), w, lane); };
+    constexpr int PF = prefetch<R>();
+    auto fetch = [&](int k, int par) __attribute__((always_inline)) {   // par: k & 1
+        S.fetch(L.u0, L.u1, plane_off<R>(k, L.logn, L.lognh), par, w, lane);
+    };
 
     // coarse correction: a wave loads the first 64 columns of its coarse row,
     // and wave 1, which stages no fine values, the last 4 of all rows (through
     // its staging registers).  Offsets carry the colour of (X + Y) in bit 0.
     R cu = 0, cr = 0;
     unsigned cg = 0;
-    int ec = 0, ed = 0;
+    int eo = 0;   // offset of the staged value's coarse row; bit 16: odd fine row
     const int lnc = L.logn - 1, ncm = (1 << lnc) - 1;
     if constexpr (PROLONG) {
         auto coff_of = [&](int row, int col) {
@@ -259,8 +288,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
         };
         cg = coff_of(w, lane);
         const int r = S.l / TXH, q = S.l - r * TXH;
-        ec = ((r >> 1) + 1) * SCW + q + 1;
-        ed = ec + ((r & 1) ? SCW : -SCW);
+        eo = (((r >> 1) + 1) * SCW + q + 1) | ((r & 1) << 16);
         if (w == 1) {
             S.g = coff_of((lane >> 2) & 7, TX + (lane & 3));
             S.l = ((lane >> 2) & 7) * SCW + TX + (lane & 3);
@@ -278,31 +306,39 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
             if (w == 1 && lane < 4 * SCH) {
                 R u, r;
                 cload(S.g, Z, u, r);
-                S.a[0] = u;
-                S.b[0] = r;
+                S.va[0][0] = u;
+                S.vb[0][0] = r;
             }
         }
     };
+    auto cplane = [&](int Z) { return sE[CARRY ? 0 : Z & 3]; };
     auto cstore = [&](int Z) {
         if constexpr (PROLONG) {
-            R *E = sE[Z & 3];
+            R *E = cplane(Z);
             E[w * SCW + lane] = cu - cr;
-            if (w == 1 && lane < 4 * SCH) E[S.l] = S.a[0] - S.b[0];
+            if (w == 1 && lane < 4 * SCH) E[S.l] = S.va[0][0] - S.vb[0][0];
         }
     };
     // the fetched plane k (par: k & 1) into its ring slot
     auto stage = [&](int k, auto par) __attribute__((always_inline)) {
+        constexpr int odd = decltype(par)::value;
         if constexpr (PROLONG) {
-            constexpr bool odd = decltype(par)::value;
-            const int Z = k >> 1;
-            S.correct(sE[Z & 3], sE[(odd ? Z + 1 : Z - 1) & 3], ec, ed, odd, w, lane);
+            const int Z = (k + 1) >> 1;
+            const int ec = eo & 0xffff, ed = ec - SCW + (eo >> 16) * (2 * SCW);
+            if (!CARRY) {
+#pragma unroll
+                for (int i = 0; i < SweepStage<R>::VW; ++i) S.xn[i][0] = S.xn[i][1] = 0;
+                S.inplane(cplane(Z - 1), ec, ed, w, lane);
+            }
+            if (odd || !CARRY) S.inplane(cplane(Z), ec, ed, w, lane);
+            if (w >= SweepStage<R>::V0 / 64 || w == 0) S.correct(ec, ed, odd);
         }
-        S.store(sS[k & 3][0] + 1, sS[k & 3][1] + 1, w, lane);
+        S.store(sS[k & 3][0] + 1, sS[k & 3][1] + 1, odd, w, lane);
     };
 
     // own column: row w, packed column lane
     int o = (w + 2) * TXH + 1 + lane;
-    unsigned coff = cell_off<R>(j0 + w, m0 + lane, L.lognh);
+    const unsigned coff0 = cell_off<R>(j0 + w, m0, L.lognh);
     // extra colour-0 column of waves 0..2
     const int ye = w == 0 ? -1 : w == 1 ? TY : (lane >> 1) - 1;
     const int qe = w < 2 ? 1 + lane : (lane & 1) ? TXH - 1 : 0;
@@ -313,7 +349,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
 
     ZPart<R> P[2] = {}, Q[2] = {};   // colour 0 and colour 1: the last two planes
     XyPart<R> q = {};                // colour 1: the last plane
-    R d0n = 0, dxn = 0, d1n = 0, f0n = 0, fxn = 0, f1n = 0;
+    // delta and f: colour 0 (own and extra) and colour 1, plane k in k % PF
+    R d0n[PF] = {}, dxn[PF] = {}, d1n[PF] = {}, f0n[PF] = {}, fxn[PF] = {}, f1n[PF] = {};
     unsigned nclamp = 0;
     auto update = [&](const ZPart<R> &above, const XyPart<R> &c, const ZPart<R> &below, R delta,
                       R f, bool count) {
@@ -330,10 +367,11 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
         constexpr bool FULL = decltype(full)::value;
         // opaque copies: the addresses derived from them are formed again in
         // every step instead of being kept in registers for the whole march
-        asm("" : "+v"(o), "+v"(oe), "+v"(coff), "+v"(coffe), "+v"(S.g), "+v"(S.l));
-        if constexpr (PROLONG) asm("" : "+v"(ec), "+v"(ed), "+v"(cg));
+        asm("" : "+v"(o), "+v"(oe), "+v"(coffe), "+v"(S.g), "+v"(S.l));
+        if constexpr (PROLONG) asm("" : "+v"(eo), "+v"(cg));
+        const unsigned coff = coff0 + (unsigned)(o - ((w + 2) * TXH + 1)) * (unsigned)sizeof(R);
         if (FULL || kp <= k1) stage(kp + 1, std::integral_constant<int, 1 - PAR>{});
-        if (FULL || kp < k1) fetch(kp + 2);
+        if (FULL || kp + PF <= k1) fetch(kp + 1 + PF, (PAR + 1 + PF) & 1);
         // coarse plane (kp >> 1) + 2, first needed for plane kp + 3 (PAR = 0)
         if constexpr (PROLONG && PAR == 0) {
             if (FULL || kp <= k1 - 2) cfetch((kp >> 1) + 2);
@@ -341,25 +379,12 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
         if constexpr (PROLONG && PAR == 1) {
             if (FULL || kp <= k1 - 1) cstore((kp + 3) >> 1);
         }
-        // delta (and f) of the next step's cells: colour 0 at plane kp,
-        // colour 1 at plane kp - 2
-        const R d0 = d0n, dx = dxn, d1 = d1n, f0 = f0n, fx = fxn, f1 = f1n;
-        if (FULL || (kp >= k0 - 1 && kp <= k1)) {
-            const size_t pl = plane_off<R>(kp, L.logn, L.lognh);
-            d0n = ld(L.d0, pl, coff);
-            if (HASF) f0n = ld(L.f0, pl, coff);
-            if (w < 3) {
-                if (extra) {
-                    dxn = ld(L.d0, pl, coffe);
-                    if (HASF) fxn = ld(L.f0, pl, coffe);
-                }
-            }
-        }
-        if (FULL || (kp >= k0 + 2 && kp <= k1 + 1)) {
-            const size_t pl = plane_off<R>(kp - 2, L.logn, L.lognh);
-            d1n = ld_once(L.d1, pl, coff);
-            if (HASF) f1n = ld_once(L.f1, pl, coff);
-        }
+        // delta and f of a cell: loaded PF steps ahead once this step's are
+        // used (colour 0 of plane kp - 1, colour 1 of plane kp - 3)
+        constexpr int SL = (1 - PAR) % PF;
+        R &d0 = d0n[SL], &dx = dxn[SL], &d1 = d1n[SL], &f0 = f0n[SL], &fx = fxn[SL], &f1 = f1n[SL];
+        const size_t pl0 = plane_off<R>(kp - 1 + PF, L.logn, L.lognh);
+        const bool next0 = FULL || (kp >= k0 - PF && kp <= k1 + 1 - PF);
         // plane views: kp and the two below it
         const R *A0 = sS[kp & 3][0] + 1, *A1 = sS[(kp - 1) & 3][0] + 1,
                 *A2 = sS[(kp - 2) & 3][0] + 1;
@@ -380,18 +405,29 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
                 if (own)
                     __builtin_nontemporal_store(nv, ptr(out0, plane_off<R>(t, L.logn, L.lognh),
                                                         coff));
-                if (w < 3) {
-                    if (extra) {
+            }
+            if (next0) {
+                d0 = ld(L.d0, pl0, coff);
+                if (HASF) f0 = ld(L.f0, pl0, coff);
+            }
+            P[PAR] = a;
+            if (w < 3) {
+                if (extra) {
+                    if (FULL || kp >= k0) {
                         const int oex = oe + ((ye + PAR + 1) & 1);
                         ZPart<R> ae, be;
+                        XyPart<R> c;
                         ae.read(A0, A0 + SSLOT, oe, oex);
                         be.read(A2, A2 + SSLOT, oe, oex);
                         c.read(A1, A1 + SSLOT, oe, oex);
                         sC[1 - PAR][oe - TXH] = update(ae, c, be, dx, fx, false);
                     }
+                    if (next0) {
+                        dx = ld(L.d0, pl0, coffe);
+                        if (HASF) fx = ld(L.f0, pl0, coffe);
+                    }
                 }
             }
-            P[PAR] = a;
         }
         if (FULL || (kp >= k0 + 1 && kp <= k1 + 2)) {
             const R *B = A2 + SSLOT, *C = sC[PAR] - TXH;
@@ -402,23 +438,39 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
                 __builtin_nontemporal_store(nv, ptr(out1, plane_off<R>(kp - 3, L.logn, L.lognh),
                                                     coff));
             }
+            if (FULL || (kp >= k0 + 3 - PF && kp <= k1 + 2 - PF)) {
+                const size_t pl = plane_off<R>(kp - 3 + PF, L.logn, L.lognh);
+                d1 = ld_once(L.d1, pl, coff);
+                if (HASF) f1 = ld_once(L.f1, pl, coff);
+            }
             Q[PAR] = a;
             q.read(B, C, o, ox);
+            // formed here: sunk to their use in the next step, they would keep
+            // every value read in a register
+            asm volatile("" : "+v"(q.ax), "+v"(q.ay), "+v"(q.nxy));
+            if constexpr (OP == OP_KMO) asm volatile("" : "+v"(q.ex), "+v"(q.ey));
         }
         __syncthreads();
     };
     constexpr std::integral_constant<int, 0> even{};
     constexpr std::integral_constant<int, 1> odd{};
-    fetch(k0 - 2);
+    fetch(k0 - 2, 0);
+    if (PF == 2) fetch(k0 - 1, 1);
     if constexpr (PROLONG) {
-        for (int Z = (k0 >> 1) - 2; Z <= k0 >> 1; ++Z) {
-            cfetch(Z);
-            cstore(Z);
+#pragma unroll
+        for (int z = -2; z <= 0; ++z) {
+            cfetch((k0 >> 1) + z);
+            cstore((k0 >> 1) + z);
+            __syncthreads();
+            if (CARRY && z < 0) {
+                const int ec = eo & 0xffff, ed = ec - SCW + (eo >> 16) * (2 * SCW);
+                S.inplane(sE[0], ec, ed, w, lane);
+                __syncthreads();
+            }
         }
-        __syncthreads();
     }
     stage(k0 - 2, even);
-    fetch(k0 - 1);
+    fetch(k0 - 2 + PF, PF & 1);
     __syncthreads();
     int kp = k0 - 2;
     auto edge = [&](int end) __attribute__((always_inline)) {
@@ -430,7 +482,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     };
     edge(k0 + 4);
 #pragma unroll 1
-    for (; kp + 1 < k1; kp += 2) {
+    for (; kp + PF < k1; kp += 2) {
         step(kp, even, std::true_type{});
         step(kp + 1, odd, std::true_type{});
     }
