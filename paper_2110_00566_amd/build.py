@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmgglam.so")
 SOURCES = ["mg_api.hip", "pm.hip", "fft.hip", "kmo_background.cpp"]
 HEADERS = ["mg_device.h", "mg_kernels.h", "mg_tiled.h", "mg_adjoint.h", "mg_adj_tiled.h",
-           "mg_adj_dgp.h", "mg_dc.h", "mg_sweep.h", "mg_small.h"]
+           "mg_adj_dgp.h", "mg_dc.h", "mg_sweep.h", "mg_resid.h", "mg_small.h"]
 ARCH = os.environ.get("MGGLAM_ARCH", "gfx950")
 
 

@@ -25,6 +25,7 @@
 #include "mg_adj_tiled.h"
 #include "mg_adjoint.h"
 #include "mg_dc.h"
+#include "mg_resid.h"
 #include "mg_small.h"
 #include "mg_sweep.h"
 
@@ -328,6 +329,12 @@ TileGeom sweep_geom(int n) {
     G.kz = kz;
     return G;
 }
+// Residual + restriction: the same blocks (kz counts coarse planes, at least 2).
+TileGeom resid_geom(int n) {
+    TileGeom G = sweep_geom(n);
+    G.kz /= 2;
+    return G;
+}
 
 unsigned tile_blocks(const TileGeom &G, int planes) {
     return (unsigned)((long)G.ntx * G.nty * (planes / G.kz));
@@ -354,13 +361,13 @@ unsigned launch_resid_restrict(const Mod &M, const LvlT<R> &L, const Coefs &Cf, 
                                double fs, R *ru0, R *ru1, R *rd0, R *rd1, double *partials,
                                unsigned long long *clamp, hipStream_t st) {
     if (tiled_op(OP) && tiled_level(L.n)) {
-        const TileGeom G = tile_geom(L.n, L.n / 2, 64);
+        const TileGeom G = resid_geom(L.n);
         const unsigned nb = tile_blocks(G, L.n / 2);
         if (L.f0)
-            k_resid_restrict_tiled<fwd_op(OP), REDUCE, true, R><<<nb, TPB, 0, st>>>(
+            k_resid_tiled<fwd_op(OP), REDUCE, true, R><<<nb, SNT, 0, st>>>(
                 M, L, fptr, fs, ru0, ru1, rd0, rd1, partials, clamp, G);
         else
-            k_resid_restrict_tiled<fwd_op(OP), REDUCE, false, R><<<nb, TPB, 0, st>>>(
+            k_resid_tiled<fwd_op(OP), REDUCE, false, R><<<nb, SNT, 0, st>>>(
                 M, L, fptr, fs, ru0, ru1, rd0, rd1, partials, clamp, G);
         return nb;
     }
@@ -1154,10 +1161,12 @@ mg_status dc_finish(const mg_opts *o, Ctx &C, DeltaIn delta, double *phi, mg_sta
     mg_status rc;
     for (;;) {
         // FP64 residual of phi64, g = -r in FP32 (its restriction is unused)
-        k_resid_restrict_tiled<OP, true, false, double, true><<<nbr, TPB, 0, C.st>>>(
+        const TileGeom Gq = resid_geom(F.n);
+        const unsigned nbq = tile_blocks(Gq, F.n / 2);
+        k_resid_tiled<OP, true, false, double, true><<<nbq, SNT, 0, C.st>>>(
             C.M, view(F, false), C.scal + S_MU64, 1.0, Hc.ru[0], Hc.ru[1], Hc.f[0], Hc.f[1],
-            C.partials, C.clamp, Gr, G.f[0], G.f[1]);
-        S64.finalize(nbr, 5);
+            C.partials, C.clamp, Gq, G.f[0], G.f[1]);
+        S64.finalize(nbq, 5);
         if ((rc = S64.read_scal(hs)) != MG_OK) return rc;
         eps = std::sqrt(hs[S_EPS64]);
         if (cycles32 + cyc < MG_HIST) st->eps_hist[cycles32 + cyc] = eps;

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(TPB) void k_corr_pass_tiled(Mod M, LvlT<float> L, c
 // arithmetic) and its restriction in FP64 into the first FP64 coarse level:
 // R(pb + e) (the coarse initial guess of the whole field) and R d.  Block
 // sums of d and d^2 (mu' and the inner norm).  Thread = coarse cell, as in
-// k_resid_restrict_tiled.
+// k_resid_restrict.
 template <int MODEL>
 __global__ __launch_bounds__(TPB) void k_corr_resid_restrict_tiled(
     Mod M, LvlT<float> L, const float *pb0, const float *pb1, const double *fptr, double *ru0,

@@ -1,7 +1,7 @@
 // LDS-tiled versions of the kernels that touch every finest-level cell
-// (colour pass, residual + restriction, prolongation, coarse source), for
-// levels with at least 128 cells per side.  The smoothing sweeps of the solves
-// are in mg_sweep.h.
+// (colour pass, prolongation, coarse source), for levels with at least 128
+// cells per side.  The smoothing sweeps of the solves are in mg_sweep.h, the
+// residual + restriction in mg_resid.h.
 //
 // A block owns a tile of TX = 64 packed x-columns (one wave wide) and TY = 8
 // rows and marches through a z-chunk.  The planes it needs are staged once in
@@ -220,9 +220,9 @@ __device__ __forceinline__ NbT<T> lds_nb(const R *Am, const R *A0, const R *Ap, 
 // Non-Laplacian term of the tiled kernels at a cell with face sum faces and
 // centre value u.  OP_NEWTON (the Newton-GS comparator) works on the
 // quadratic form: Sigma/alpha - 2 D^2/(3 alpha), D = (faces - 6u)/h^2.
-template <int OP, typename T, typename L_>
-__device__ __forceinline__ T tiled_term(const Mod &M, const L_ &L, const NbT<T> &s, T delta,
-                                        T faces, T u, unsigned long long *clamp) {
+template <int OP, typename T, typename L_, typename S_, typename Clamp>
+__device__ __forceinline__ T tiled_term(const Mod &M, const L_ &L, const S_ &s, T delta, T faces,
+                                        T u, Clamp *clamp) {
     if constexpr (OP == OP_NEWTON)
         return newton_term<T>(M, dgp_sigma_over_alpha<T>(M, L, s, delta),
                               (faces - (T)6 * u) / (T)L.h2);
@@ -308,146 +308,6 @@ __global__ __launch_bounds__(TPB) void k_pass_tiled(Mod M, Lvl L, int c, double 
         }
         __syncthreads();
     }
-}
-
-// Residual + restriction (see k_resid_restrict) for a tile of 64 x 4 coarse
-// cells.  The block marches over the fine planes of its coarse z-chunk with a
-// ring of 3 staged planes of both colours, like the pass; a thread owns one
-// coarse cell and computes its 4 children in each fine plane (rows 2ty,
-// 2ty+1, both colours), summing over the two fine planes of the coarse
-// plane.  kz counts coarse planes.  HASF: the level has a right-hand side f
-// (every level but the finest).
-// WG: also store g = -d of every fine cell in FP32 (g0/g1, the packed
-// colours; the outer step of the defect-correction solve).
-template <int OP, bool REDUCE, bool HASF, typename R, bool WG = false>
-__global__ __launch_bounds__(TPB) void k_resid_restrict_tiled(Mod M, LvlT<R> L, const double *fptr,
-                                                              double fscale, R *ru0, R *ru1,
-                                                              R *rd0, R *rd1, double *partials,
-                                                              unsigned long long *clamp,
-                                                              TileGeom G, float *g0 = nullptr,
-                                                              float *g1 = nullptr) {
-    __shared__ __align__(16) R s0[3][TSLOT], s1[3][TSLOT];
-    const size_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const int bx = (int)(blk % G.ntx);
-    const int by = (int)((blk / G.ntx) % G.nty);
-    const int bz = (int)(blk / ((size_t)G.ntx * G.nty));
-    // fine tile: packed columns m0.., fine rows j0 .. j0+7 (coarse rows j0/2 ..)
-    const int m0 = bx * TX, j0 = by * TY, k0 = 2 * bz * G.kz, k1 = k0 + 2 * G.kz;
-    const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-    const int lnc = L.logn - 1;
-    unsigned coff[2];
-    Stage2<R> S;
-    S.init(tid, j0, m0, L.logn, L.lognh);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) coff[b] = cell_off<R>(j0 + 2 * ty + b, m0 + tx, L.lognh);
-    auto fetch = [&](int k) { S.fetch(L.u0, L.u1, plane_off<R>(k, L.logn, L.lognh), tid); };
-    auto store = [&](int slot) { S.store(s0[slot] + 1, s1[slot] + 1, tid); };
-    // delta (and f) of the 4 children in a fine plane, one plane ahead
-    R dn[4], fn[4];
-    auto fetch_cells = [&](int k) {
-        const size_t pl = plane_off<R>(k, L.logn, L.lognh);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            dn[2 * b] = ld_once(L.d0, pl, coff[b]);
-            dn[2 * b + 1] = ld_once(L.d1, pl, coff[b]);
-            if (HASF) {
-                fn[2 * b] = ld_once(L.f0, pl, coff[b]);
-                fn[2 * b + 1] = ld_once(L.f1, pl, coff[b]);
-            }
-        }
-    };
-    // slot of fine plane k: (k - k0 + 1) mod 3
-    fetch(k0 - 1);
-    store(0);
-    fetch(k0);
-    store(1);
-    fetch(k0 + 1);
-    fetch_cells(k0);
-    double su = 0.0, sd = 0.0, acc1 = 0.0, acc2 = 0.0;
-    const double fs = fptr ? fscale * (*fptr) : 0.0;
-    const double inv_h2 = 1.0 / L.h2;
-    for (int k = k0; k < k1; ++k) {
-        const int sm = (k - k0) % 3, sz = (k - k0 + 1) % 3, sp = (k - k0 + 2) % 3;
-        store(sp);
-        R dc[4], fc[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            dc[q] = dn[q];
-            fc[q] = HASF ? fn[q] : R(0);
-        }
-        __syncthreads();
-        if (k + 2 <= k1) fetch(k + 2);
-        if (k + 1 < k1) fetch_cells(k + 1);
-        // dv, fv: delta and f of child (b, c), passed by value so that the
-        // rolled loop indexes no local array (that would put dc, fc in scratch)
-        auto child = [&](int b, int c, R dv, R fv) {
-            const int row = 2 * ty + b;
-            const int p = (j0 + row + k + c) & 1;
-            const R *Am = (c ? s1[sm] : s0[sm]) + 1;
-            const R *A0 = (c ? s1[sz] : s0[sz]) + 1;
-            const R *Ap = (c ? s1[sp] : s0[sp]) + 1;
-            const R *Bm = (c ? s0[sm] : s1[sm]) + 1;
-            const R *B0 = (c ? s0[sz] : s1[sz]) + 1;
-            const R *Bp = (c ? s0[sp] : s1[sp]) + 1;
-            const int r = row + 1, q = tx + 1;
-            const double u = (double)A0[r * TXH + q];
-            const double f = (HASF ? (double)fv : 0.0) + fs;
-            double d;
-            if constexpr (sizeof(R) == 4 && (OP == OP_DGP || OP == OP_KMO)) {
-                // FP32 storage: the Laplacian in double, the model term in
-                // float (nDGP) or from float stencil combinations (Kmouflage)
-                const NbT<float> s = lds_nb<float, R>(Am, A0, Ap, B0, Bm, Bp, r, q, p);
-                const double faces = ((double)s.xp + (double)s.xm) +
-                                     ((double)s.yp + (double)s.ym) +
-                                     ((double)s.zp + (double)s.zm);
-                d = (faces - 6.0 * u) * inv_h2 -
-                    (double)model_term<OP, float>(M, L, s, (float)dv, clamp) - f;
-            } else {
-                const Nb s = lds_nb<double, R>(Am, A0, Ap, B0, Bm, Bp, r, q, p);
-                const double faces = (s.xp + s.xm) + (s.yp + s.ym) + (s.zp + s.zm);
-                d = (faces - 6.0 * u) * inv_h2 -
-                    tiled_term<OP, double>(M, L, s, (double)dv, faces, u, clamp) - f;
-            }
-            sd += d;
-            su += u;
-            if (REDUCE) {
-                acc1 += d;
-                acc2 += d * d;
-            }
-            if (WG)
-                *ptr(c ? g1 : g0, plane_off<float>(k, L.logn, L.lognh),
-                     cell_off<float>(j0 + row, m0 + tx, L.lognh)) = (float)(-d);
-        };
-        if constexpr (sizeof(R) == 4 && OP == OP_DGP) {
-            // FP32 nDGP (70 registers rolled, 96 unrolled, 3% faster): the
-            // four children unrolled
-            child(0, 0, dc[0], fc[0]);
-            child(0, 1, dc[1], fc[1]);
-            child(1, 0, dc[2], fc[2]);
-            child(1, 1, dc[3], fc[3]);
-        } else {
-            // the four children stay rolled (unrolled, the Kmouflage term
-            // needs 200+ registers per lane; rolled the FP64 kernel is 4%
-            // faster)
-#pragma unroll 1
-            for (int q = 0; q < 4; ++q) {
-                const R dv = q == 0 ? dc[0] : q == 1 ? dc[1] : q == 2 ? dc[2] : dc[3];
-                const R fv = q == 0 ? fc[0] : q == 1 ? fc[1] : q == 2 ? fc[2] : fc[3];
-                child(q >> 1, q & 1, dv, fv);
-            }
-        }
-        if (k & 1) {
-            const int K = k >> 1, I = m0 + tx, J = (j0 >> 1) + ty;
-            const size_t cidx = ((size_t)K << (2 * lnc - 1)) + ((size_t)J << (lnc - 1)) + (I >> 1);
-            const int ccol = (I + J + K) & 1;
-            (ccol ? ru1 : ru0)[cidx] = (R)(0.125 * su);
-            (ccol ? rd1 : rd0)[cidx] = (R)(0.125 * sd);
-            su = 0.0;
-            sd = 0.0;
-        }
-        __syncthreads();
-    }
-    if (REDUCE) block_sum2(acc1, acc2, partials, blk);
 }
 
 // u_fine += P(uc - rc) (see k_prolong) with the coarse difference staged in
@@ -583,7 +443,8 @@ __global__ __launch_bounds__(TPB) void k_coarse_source_tiled(Mod M, LvlT<R> Lc, 
             R *S = ptr(c ? s1 : s0, pl, o);
             const double rd = (double)ld_once(c ? s1 : s0, pl, o) - sh;
             *S = (R)((faces - 6.0 * (double)ru) / Lc.h2
-                     - tiled_term<OP, double>(M, Lc, s, delta, faces, (double)ru, nullptr) - rd);
+                     - tiled_term<OP, double>(M, Lc, s, delta, faces, (double)ru,
+                                                (unsigned long long *)nullptr) - rd);
             *ptr(c ? u1 : u0, pl, o) = ru;
         }
         __syncthreads();
