@@ -170,6 +170,34 @@ __device__ __forceinline__ double sqrt_normal(double x) {
     g = fma(fma(-g, g, x), h, g);
     return fma(fma(-g, g, x), h, g);
 }
+// The same in FP32 (x > 2^-96), rounded as sqrtf() rounds.
+__device__ __forceinline__ float sqrt_normal(float x) {
+    const float y = __builtin_amdgcn_rsqf(x);
+    float g = x * y, h = 0.5f * y;
+    const float r = fmaf(-h, g, 0.5f);
+    g = fmaf(g, r, g);
+    h = fmaf(h, r, h);
+    return fmaf(fmaf(-g, g, x), h, g);
+}
+
+// a / b, rounded as the division rounds, where b, 1/b and the quotient (or
+// a = 0) are normal numbers: a Newton step on the hardware's reciprocal
+// estimate (two in FP64) and two residual corrections of the quotient, the
+// division without its scaling and special-case instructions.
+__device__ __forceinline__ float div_normal(float a, float b) {
+    float r = __builtin_amdgcn_rcpf(b);
+    r = fmaf(fmaf(-b, r, 1.0f), r, r);
+    float q = a * r;
+    q = fmaf(fmaf(-b, q, a), r, q);
+    return fmaf(fmaf(-b, q, a), r, q);
+}
+__device__ __forceinline__ double div_normal(double a, double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(fma(-b, r, 1.0), r, r);
+    r = fma(fma(-b, r, 1.0), r, r);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
 
 // clamp: count of clamped discriminants, a device counter (added to with an
 // atomic; may be null) or the calling thread's own.
@@ -197,11 +225,12 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
             const float sig = fmaf((float)M.s, delta,
                                    fmaf(u3, (float)L.c3h4, u8 * (float)L.c8h4));
             const float disc = fmaf(8.0f / 3.0f, sig, (float)(M.alpha * M.alpha));
-            if (disc < 0.0f) {
-                count_clamp(clamp);
-                return (T)(-0.75 * M.alpha);
-            }
-            return 2.0f * sig / fmaf((float)M.sgn, sqrtf(disc), (float)M.alpha);
+            const bool neg = disc < 0.0f;
+            if (neg) count_clamp(clamp);
+            // root 1e-14 at least: nothing beside alpha
+            const float root = sqrt_normal(disc < 1e-28f ? 1e-28f : disc);
+            const float K = div_normal(2.0f * sig, fmaf((float)M.sgn, root, (float)M.alpha));
+            return neg ? (T)(-0.75 * M.alpha) : K;
         }
         const T t3 = dxy * dxy + dxz * dxz + dyz * dyz;
         const T t8 = s.nxy * s.nxy + s.nxz * s.nxz + s.nyz * s.nyz;
@@ -229,7 +258,8 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
         float gn2 = 1.0f;
         for (int t = 0; t < M.nk - 2; ++t) gn2 *= g;
         const float sig1 = fmaf(g, gn2 * (float)M.a1, (float)M.c0);
-        return fmaf(delta, (float)M.src, q * (gn2 * (float)M.b2)) / ((float)M.ctil * sig1);
+        return div_normal(fmaf(delta, (float)M.src, q * (gn2 * (float)M.b2)),
+                          (float)M.ctil * sig1);
     }
     const double g = (double)(ex * ex + ey * ey + ez * ez) * L.c4h2;
     const double q = (double)(ex * ex * (2 * ax - ay - az) + ey * ey * (2 * ay - ax - az)
@@ -239,7 +269,7 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
     for (int t = 0; t < M.nk - 2; ++t) gn2 *= g;
     const double sig1 = M.c0 + M.a1 * gn2 * g;
     const double sig2 = M.b2 * gn2 * q;
-    return (T)((M.src * (double)delta + sig2) / (M.ctil * sig1));
+    return (T)div_normal(M.src * (double)delta + sig2, M.ctil * sig1);
 }
 
 template <int MODEL, typename T, typename L_, typename Clamp>
