@@ -144,6 +144,9 @@ typedef struct {
                                    hands over to FP64 without a separate evaluation) */
     double level_ms[MG_LEVELS]; /* profile=1: GPU time of the cycles' work on each level
                                    (0 = finest), summed over all cycles and both precisions;
+                                   what forms a level's coarse source counts to the next finer
+                                   one (also where it is one launch with the level's first
+                                   sweep: FP64, n >= 128, not Kmouflage);
                                    the levels of the single-workgroup tail (<= 16^3) are
                                    reported together at the tail's first level; the residual
                                    evaluations outside the cycles are not included */

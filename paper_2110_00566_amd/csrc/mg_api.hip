@@ -598,10 +598,13 @@ struct Solver {
     template <bool PROLONG>
     void launch_sweep(int l) {
         HLevel<R> &H = Hh.lv[l];
-        SweepCoarse<R> K{};
+        SweepArgs<R> K{};
         if (PROLONG) {
             const HLevel<R> &Hc = Hh.lv[l + 1];
-            K = {Hc.u[0], Hc.u[1], Hc.ru[0], Hc.ru[1]};
+            K.u0 = Hc.u[0];
+            K.u1 = Hc.u[1];
+            K.r0 = Hc.ru[0];
+            K.r1 = Hc.ru[1];
         }
         const TileGeom G = sweep_geom(H.n);
         const unsigned nb = tile_blocks(G, H.n);
@@ -614,7 +617,38 @@ struct Solver {
         std::swap(H.u[0], H.spare);
         std::swap(H.u[1], H.spare2);
     }
+    // The first sweep of a cycle on a coarse level, with the level's source
+    // formed in the same launch.  FP64 only: from FP32 storage the source is
+    // evaluated in double, the sweep in float.  Not Kmouflage, whose kernel has
+    // no registers for both (it spills).  256^3: 137 us for 118 + 113 us, 128^3:
+    // 25 us for 19 + 22 us.
+    bool source_in_sweep(int lc) const {
+        return sizeof(R) == 8 && OP != OP_KMO && fused_sweep(lc) &&
+               (lc == Hh.nlev - 1 ? C.nuc : C.nu1) >= 1;
+    }
+    bool swept = false;   // the next sweep ran with the source
+    void source_sweep(int l) {
+        if constexpr (tiled_op(OP) && OP != OP_KMO && sizeof(R) == 8) {
+            HLevel<R> &H = Hh.lv[l];
+            SweepArgs<R> K{};
+            K.s0 = H.spare;
+            K.s1 = H.spare2;
+            K.shift = l == 1 ? C.scal + S_SHIFT : nullptr;
+            LvlT<R> L = view(H, true);
+            L.u0 = H.ru[0];
+            L.u1 = H.ru[1];
+            const TileGeom G = sweep_geom(H.n);
+            k_sweep_tiled<OP, R, true, false, true><<<tile_blocks(G, H.n), SNT, 0, C.st>>>(
+                C.M, L, H.u[0], H.u[1], K, nullptr, 0.0, C.clamp, G);
+            std::swap(H.f[0], H.spare);
+            std::swap(H.f[1], H.spare2);
+        }
+    }
     void sweep(int l) {
+        if (swept) {
+            swept = false;
+            return;
+        }
         if (!fused_sweep(l)) {
             pass(l, 0);
             pass(l, 1);
@@ -738,6 +772,11 @@ struct Solver {
     bool source_in_tail(int lc) const { return !ADJ && C.cycle == 0 && lc == tail_start(); }
     void coarse_source(int lc) {
         if (source_in_tail(lc)) return;
+        if (source_in_sweep(lc)) {   // the sweep that follows included
+            source_sweep(lc);
+            swept = true;
+            return;
+        }
         HLevel<R> &Hc = Hh.lv[lc];
         LvlT<R> L = view(Hc, false);
         L.u0 = Hc.ru[0];

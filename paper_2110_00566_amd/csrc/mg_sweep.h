@@ -233,19 +233,29 @@ __device__ __forceinline__ CombT<R> col_comb(const ZPart<R> &above, const XyPart
     return s;
 }
 
-// coarse level of a prolongation: the correction is u - Ru
+// PROLONG: the coarse level, whose correction is u - Ru.  SOURCE: where the
+// level's FAS source goes (s0, s1), and the shift of its restricted residual
+// (null: 0).
 template <typename R>
-struct SweepCoarse {
+struct SweepArgs {
     const R *u0, *u1, *r0, *r1;
+    R *s0, *s1;
+    const double *shift;
 };
 
 // PROLONG: the sweep starts from the prolonged field (first post-smoothing
 // sweep): the coarse correction is added while the planes are staged.
-template <int OP, typename R, bool HASF, bool PROLONG>
+// SOURCE: the sweep of a coarse level that follows a restriction.  The level's
+// field is R u (L.u) and L.f is R d; the launch forms S = L(R u) - (R d -
+// shift) from the planes that it stages anyway, stores it and takes it as the
+// right-hand side, so that R u is not copied and S not read back (256^3 FP64:
+// 48 B per cell less).  S goes to other arrays than R d: blocks read R d of
+// their neighbours' cells.
+template <int OP, typename R, bool HASF, bool PROLONG, bool SOURCE = false>
 __global__ __launch_bounds__(SNT)
 __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *__restrict__ out0,
                                                            R *__restrict__ out1,
-                                                           SweepCoarse<R> K, const double *fptr,
+                                                           SweepArgs<R> K, const double *fptr,
                                                            double fscale,
                                                            unsigned long long *clamp,
                                                            TileGeom G) {
@@ -266,6 +276,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const R fs = uniform((R)(fptr ? fscale * (*fptr) : 0.0));
+    static_assert(!SOURCE || (HASF && !PROLONG), "the source is the right-hand side");
+    const R shift = uniform((R)(SOURCE && K.shift ? *K.shift : 0.0));
+    const R inv_h2 = uniform((R)(1.0 / L.h2));
     SweepStage<R> S;
     S.init(tid, j0, m0, L.logn, L.lognh);
     constexpr int PF = prefetch<R>();
@@ -352,11 +365,16 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     // delta and f: colour 0 (own and extra) and colour 1, plane k in k % PF
     R d0n[PF] = {}, dxn[PF] = {}, d1n[PF] = {}, f0n[PF] = {}, fxn[PF] = {}, f1n[PF] = {};
     unsigned nclamp = 0;
-    auto update = [&](const ZPart<R> &above, const XyPart<R> &c, const ZPart<R> &below, R delta,
-                      R f, bool count) {
-        const CombT<R> s = col_comb(above, c, below);
+    XyPart<R> qs = {};               // SOURCE: the same, of the old field
+    R Qs[2] = {};
+    auto source = [&](const CombT<R> &s, R u, R delta, R rd) {
+        return (s.faces() - (R)6 * u) * inv_h2 -
+               tiled_term<OP, R>(M, L, s, delta, s.faces(), u, (unsigned long long *)nullptr) -
+               (rd - shift);
+    };
+    auto update = [&](const CombT<R> &s, R u, R delta, R f, bool count) {
         unsigned neg = 0;
-        const R nv = tiled_update<OP, R>(M, L, s, delta, s.faces(), c.u, f + fs, &neg);
+        const R nv = tiled_update<OP, R>(M, L, s, delta, s.faces(), u, f + fs, &neg);
         if (count) nclamp += neg;
         return nv;
     };
@@ -400,7 +418,12 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
                 const bool own = FULL || (t >= k0 && t < k1);
                 XyPart<R> c;
                 c.read(A1, A1 + SSLOT, o, ox);
-                const R nv = update(a, c, P[PAR], d0, f0, own);
+                const CombT<R> s = col_comb(a, c, P[PAR]);
+                if (SOURCE) {
+                    f0 = source(s, c.u, d0, f0);
+                    if (own) *ptr(K.s0, plane_off<R>(t, L.logn, L.lognh), coff) = f0;
+                }
+                const R nv = update(s, c.u, d0, f0, own);
                 sC[1 - PAR][o - TXH] = nv;
                 if (own)
                     __builtin_nontemporal_store(nv, ptr(out0, plane_off<R>(t, L.logn, L.lognh),
@@ -420,7 +443,9 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
                         ae.read(A0, A0 + SSLOT, oe, oex);
                         be.read(A2, A2 + SSLOT, oe, oex);
                         c.read(A1, A1 + SSLOT, oe, oex);
-                        sC[1 - PAR][oe - TXH] = update(ae, c, be, dx, fx, false);
+                        const CombT<R> s = col_comb(ae, c, be);
+                        if (SOURCE) fx = source(s, c.u, dx, fx);
+                        sC[1 - PAR][oe - TXH] = update(s, c.u, dx, fx, false);
                     }
                     if (next0) {
                         dx = ld(L.d0, pl0, coffe);
@@ -434,7 +459,19 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
             ZPart<R> a;
             a.read(B, C, o, oy);
             if (FULL || kp >= k0 + 3) {
-                const R nv = update(a, q, Q[PAR], d1, f1, true);
+                const CombT<R> s = col_comb(a, q, Q[PAR]);
+                if (SOURCE) {   // the old field: other face neighbours
+                    CombT<R> z = s;
+                    z.ax = qs.ax;
+                    z.ay = qs.ay;
+                    z.ex = qs.ex;
+                    z.ey = qs.ey;
+                    z.az = A2[o] + Qs[PAR];
+                    z.ez = A2[o] - Qs[PAR];
+                    f1 = source(z, q.u, d1, f1);
+                    *ptr(K.s1, plane_off<R>(kp - 3, L.logn, L.lognh), coff) = f1;
+                }
+                const R nv = update(s, q.u, d1, f1, true);
                 __builtin_nontemporal_store(nv, ptr(out1, plane_off<R>(kp - 3, L.logn, L.lognh),
                                                     coff));
             }
@@ -449,6 +486,16 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
             // every value read in a register
             asm volatile("" : "+v"(q.ax), "+v"(q.ay), "+v"(q.nxy));
             if constexpr (OP == OP_KMO) asm volatile("" : "+v"(q.ex), "+v"(q.ey));
+            if constexpr (SOURCE) {
+                Qs[PAR] = A2[o];
+                const R xp = A2[ox], xm = A2[ox - 1], yp = A2[o + TXH], ym = A2[o - TXH];
+                qs.ax = xp + xm;
+                qs.ay = yp + ym;
+                qs.ex = xp - xm;
+                qs.ey = yp - ym;
+                asm volatile("" : "+v"(qs.ax), "+v"(qs.ay));
+                if constexpr (OP == OP_KMO) asm volatile("" : "+v"(qs.ex), "+v"(qs.ey));
+            }
         }
         __syncthreads();
     };
