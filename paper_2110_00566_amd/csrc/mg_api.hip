@@ -1071,18 +1071,28 @@ struct DeltaIn {
     bool f32;
 };
 
+// Natural field -> packed colours f of level F and, below it, the 8-cell means
+// c of the next level (null: there is none).
+template <typename Rin, typename R>
+void pack_restrict(Ctx &C, const Rin *nat, const HLevel<R> &F, R *const f[2], R *const c[2]) {
+    if (c)
+        k_pack_restrict<Rin, R><<<nblocks(F.half / 4), TPB, 0, C.st>>>(nat, F.logn, f[0], f[1],
+                                                                       c[0], c[1]);
+    else
+        k_pack<Rin, R><<<nblocks(2 * F.half), TPB, 0, C.st>>>(nat, F.logn, f[0], f[1], nullptr);
+}
+
 // Pack delta into the finest level of hierarchy R and restrict it down.
 template <typename R>
 void density_hierarchy(Ctx &C, DeltaIn delta) {
     Hier<R> &Hh = hier<R>(C);
-    HLevel<R> &F = Hh.lv[0];
     if (delta.f32)
-        k_pack<float, R><<<nblocks(2 * F.half), TPB, 0, C.st>>>(
-            static_cast<const float *>(delta.p), F.logn, F.d[0], F.d[1], nullptr);
+        pack_restrict(C, static_cast<const float *>(delta.p), Hh.lv[0], Hh.lv[0].d,
+                      Hh.nlev > 1 ? Hh.lv[1].d : nullptr);
     else
-        k_pack<double, R><<<nblocks(2 * F.half), TPB, 0, C.st>>>(
-            static_cast<const double *>(delta.p), F.logn, F.d[0], F.d[1], nullptr);
-    for (int l = 0; l + 1 < Hh.nlev; ++l) {
+        pack_restrict(C, static_cast<const double *>(delta.p), Hh.lv[0], Hh.lv[0].d,
+                      Hh.nlev > 1 ? Hh.lv[1].d : nullptr);
+    for (int l = 1; l + 1 < Hh.nlev; ++l) {
         HLevel<R> &H = Hh.lv[l], &Hc = Hh.lv[l + 1];
         k_restrict<R><<<nblocks(2 * Hc.half), TPB, 0, C.st>>>(H.d[0], H.d[1], H.logn, Hc.d[0],
                                                              Hc.d[1]);
@@ -1347,13 +1357,11 @@ template <int MODEL>
 void adj_coefficients(Ctx &C, const double *phi) {
     // linearisation points: packed phi on the finest level, restricted below
     Hier<double> &Hh = C.h64;
-    HLevel<double> &F = Hh.lv[0];
-    k_pack<double, double><<<nblocks(2 * F.half), TPB, 0, C.st>>>(phi, F.logn, F.lin[0],
-                                                                  F.lin[1], nullptr);
+    pack_restrict(C, phi, Hh.lv[0], Hh.lv[0].lin, Hh.nlev > 1 ? Hh.lv[1].lin : nullptr);
     for (int l = 0; l < Hh.nlev; ++l) {
         HLevel<double> &H = Hh.lv[l];
         alias_face_coefs(H, MODEL != MODEL_KMO);
-        if (l + 1 < Hh.nlev) {
+        if (l > 0 && l + 1 < Hh.nlev) {
             HLevel<double> &Hc = Hh.lv[l + 1];
             k_restrict<double><<<nblocks(2 * Hc.half), TPB, 0, C.st>>>(H.lin[0], H.lin[1], H.logn,
                                                                       Hc.lin[0], Hc.lin[1]);
