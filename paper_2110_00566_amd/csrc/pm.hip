@@ -96,125 +96,147 @@ __global__ __launch_bounds__(PTPB) void k_cic_link(const float *__restrict__ pos
     next[t] = atomicExch(head + c, t);
 }
 
-// Block-wide exclusive prefix sum of v over the PTPB threads (every thread
-// calls it); *total receives the sum.
-__device__ __forceinline__ int block_scan(int v, int *total) {
-    __shared__ int wsum[PTPB / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    int base = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < PTPB / 64; ++k) {
-        if (k < w) base += wsum[k];
-        tot += wsum[k];
-    }
-    *total = tot;
-    __syncthreads();
-    return base + x - v;
-}
-
-// Every particle in the NL lists of a block (list l starts at head[cell(l)]),
-// handed to body(p, l) with all lanes busy: the lists are walked once to
-// count them, the counts are scanned, and the (particle, list) pairs go into
-// an LDS queue of KQ entries that all threads then drain; a tile with more
-// than KQ particles takes several rounds (each walks the lists again).  The
-// list, not the particle's position, says where it lies relative to the
-// tile: on a mesh one tile wide the halo list below x = 0 is the tile's own
-// last column.  With about
-// one particle per eight cells, walking the lists directly would run the
-// particle work once per list with most lanes idle.
-constexpr int KQ = 1024;
-
-template <int NL, class Cell, class Body>
-__device__ __forceinline__ void tile_particles(const int *__restrict__ head,
-                                               const int *__restrict__ next, Cell cell,
-                                               int2 *queue, Body body) {
-    constexpr int NR = (NL + PTPB - 1) / PTPB;
-    int hd[NR], cnt = 0;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int l = threadIdx.x + r * PTPB;
-        hd[r] = l < NL ? head[cell(l)] : -1;
-    }
-#pragma unroll 1
-    for (int r = 0; r < NR; ++r)
-        for (int p = hd[r]; p >= 0; p = next[p]) ++cnt;
-    int total;
-    const int off = block_scan(cnt, &total);
-    for (int base = 0; base < total; base += KQ) {
-        int v = off;
-#pragma unroll 1
-        for (int r = 0; r < NR && v < base + KQ; ++r)
-            for (int p = hd[r]; p >= 0 && v < base + KQ; p = next[p], ++v)
-                if (v >= base) queue[v - base] = make_int2(p, threadIdx.x + r * PTPB);
-        __syncthreads();
-        const int m = total - base < KQ ? total - base : KQ;
-        for (int e = threadIdx.x; e < m; e += PTPB) body(queue[e].x, queue[e].y);
-        __syncthreads();
-    }
-}
-
-// A block owns a tile of CGX x CGY x CGZ cells and walks, once, the lists
-// of every corner cell whose particles reach the tile (the tile and one cell
-// below it in each axis), adding the fixed-point weights that land inside
-// the tile into LDS; then it writes the tile's delta.
-// 32 x 8 x 8 walks 1.31 lists per cell (32 x 4 x 4: 1.61) and ran 16% faster
-// on 256^3 particles over 512^3 cells than 32 x 4 x 4; taller or wider tiles
-// were slower (fewer blocks per CU).
+// A block owns a tile of CGX x CGY x CGZ cells and walks the lists of every
+// corner cell whose particles reach the tile (the tile and one cell below it
+// in each axis), adding the fixed-point weights that land inside the tile
+// into LDS; then it writes the tile's delta.
+//
+// The walk is a chain of dependent loads, so a thread advances all its lists
+// together, one particle a round (one list after another took the sum of
+// their lengths in load latencies, twice: to count the particles and to queue
+// them).  A round's particles go into an LDS queue, in no particular order,
+// which all threads drain when it is full or the lists have ended: with one
+// particle per eight cells, most lanes have none.  The list, not the particle's
+// position, says where it lies relative to the tile: on a mesh one tile wide
+// the halo list below x = 0 is the tile's own last column.
+// 256^3 particles on 256^3 cells: 162 us (408 us list by list); what is left is
+// the latency of the longest lists, some ten loads, and the weights.
 constexpr int CGX = 32, CGY = 8, CGZ = 8;
 constexpr int CG_CELLS = CGX * CGY * CGZ;                      // 2048
 constexpr int CG_LISTS = (CGX + 1) * (CGY + 1) * (CGZ + 1);    // 2673
+constexpr int GTPB = 512;
+constexpr int CG_NR = (CG_LISTS + GTPB - 1) / GTPB;            // lists per thread
+constexpr int KQ = 2048;   // queue entries
+static_assert(KQ >= 64 * CG_NR, "a wave's round fits into an empty queue");
+// accumulators: the tile and a cell around it, which takes the weights that
+// fall outside, so that no deposit is tested (40 KB with the queue: four
+// blocks per CU)
+constexpr int CPX = CGX + 2, CPY = CGY + 2, CG_ACC = CPX * CPY * (CGZ + 2);
 
 template <typename T>
-__global__ __launch_bounds__(PTPB) void k_cic_gather(const float *__restrict__ pos, int logn,
+__global__ __launch_bounds__(GTPB) void k_cic_gather(const float *__restrict__ pos, int logn,
                                                       const int *__restrict__ head,
                                                       const int *__restrict__ next, double scale,
                                                       T *__restrict__ delta) {
-    __shared__ unsigned long long acc[CG_CELLS];
-    __shared__ int2 queue[KQ];
+    __shared__ unsigned long long acc[CG_ACC];
+    __shared__ int qp[KQ];               // queued particles
+    __shared__ unsigned short ql[KQ];    // and their corner cells
+    __shared__ int qn, qend;             // entries asked for; end of the queue if some did not fit
     const int nm1 = (1 << logn) - 1;
     const int ntx = (1 << logn) / CGX, nty = (1 << logn) / CGY;
     const int blk = (int)xcd_chunk(blockIdx.x, gridDim.x);
     const int bx = blk % ntx, by = (blk / ntx) % nty, bz = blk / (ntx * nty);
     const int x0 = bx * CGX, y0 = by * CGY, z0 = bz * CGZ;
-    for (int q = threadIdx.x; q < CG_CELLS; q += PTPB) acc[q] = 0ull;
-    // lists of the corner cells whose clouds reach the tile: the tile and
-    // one cell below it in each axis
-    auto cell = [&](int q) {
-        const int lx = q % (CGX + 1) - 1, ly = (q / (CGX + 1)) % (CGY + 1) - 1,
-                  lz = q / ((CGX + 1) * (CGY + 1)) - 1;
-        return ((size_t)((z0 + lz) & nm1) << (2 * logn)) + ((size_t)((y0 + ly) & nm1) << logn) +
-               (size_t)((x0 + lx) & nm1);
+    const int tid = threadIdx.x;
+    int p[CG_NR];
+    unsigned short lc[CG_NR];   // accumulator of the corner cell
+#pragma unroll
+    for (int r = 0; r < CG_NR; ++r) {
+        const int q = tid + r * GTPB;
+        const int lx = q % (CGX + 1), ly = (q / (CGX + 1)) % (CGY + 1),
+                  lz = q / ((CGX + 1) * (CGY + 1));
+        lc[r] = (unsigned short)((lz * CPY + ly) * CPX + lx);
+        p[r] = -1;
+        if (q < CG_LISTS)
+            p[r] = head[((size_t)((z0 + lz - 1) & nm1) << (2 * logn)) +
+                        ((size_t)((y0 + ly - 1) & nm1) << logn) + (size_t)((x0 + lx - 1) & nm1)];
+    }
+    for (int q = tid; q < CG_ACC; q += GTPB) acc[q] = 0ull;
+    if (tid == 0) {
+        qn = 0;
+        qend = KQ;
+    }
+    __syncthreads();
+    // 2^32 w <= 2^32, rounded to an integer by the addition of 2^52, whose bits
+    // are then taken off
+    auto fixed = [](double w) {
+        const double v = fma(w, FIX_SCALE, 0x1p52);
+        return (unsigned long long)(unsigned)(__double2hiint(v) - 0x43300000) << 32 |
+               (unsigned)__double2loint(v);
     };
-    auto deposit = [&](int p, int q) {
+    auto deposit = [&](const float *x, int cell) {
         double f[3];
         int i0[3];
-        cic_weights(pos + 3 * (size_t)p, f, i0);
-        // the list's corner cell in tile coordinates (-1 .. CG-1)
-        const int lx = q % (CGX + 1) - 1, ly = (q / (CGX + 1)) % (CGY + 1) - 1,
-                  lz = q / ((CGX + 1) * (CGY + 1)) - 1;
+        cic_weights(x, f, i0);
 #pragma unroll
         for (int o = 0; o < 8; ++o) {
             const int a = o & 1, b = (o >> 1) & 1, c = o >> 2;
-            const int tx = lx + a, ty = ly + b, tz = lz + c;
-            if (tx < 0 || tx >= CGX || ty < 0 || ty >= CGY || tz < 0 || tz >= CGZ) continue;
             const double w =
                 ((a ? f[0] : 1.0 - f[0]) * (b ? f[1] : 1.0 - f[1])) * (c ? f[2] : 1.0 - f[2]);
-            atomicAdd(acc + (tz * CGY + ty) * CGX + tx, __double2ull_rn(w * FIX_SCALE));
+            atomicAdd(acc + cell + (c * CPY + b) * CPX + a, fixed(w));
         }
     };
-    tile_particles<CG_LISTS>(head, next, cell, queue, deposit);
-    for (int q = threadIdx.x; q < CG_CELLS; q += PTPB) {
+    for (;;) {
+        // a wave goes on while the queue has room for its next particles
+        bool more = false;
+        for (;;) {
+            int n = 0;
+#pragma unroll
+            for (int r = 0; r < CG_NR; ++r) n += __popcll(__ballot(p[r] >= 0));
+            if (n == 0) break;
+            int base = 0;
+            if ((tid & 63) == 0) base = atomicAdd(&qn, n);
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (base + n > KQ) {   // the entries before it are the queue
+                if ((tid & 63) == 0) atomicMin(&qend, base);
+                more = true;
+                break;
+            }
+#pragma unroll
+            for (int r = 0; r < CG_NR; ++r) {
+                const unsigned long long m = __ballot(p[r] >= 0);
+                if (m == 0) continue;
+                if (p[r] >= 0) {
+                    const int e = base + (int)__builtin_amdgcn_mbcnt_hi(
+                                             (unsigned)(m >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+                    qp[e] = p[r];
+                    ql[e] = lc[r];
+                    p[r] = next[p[r]];
+                }
+                base += __popcll(m);
+            }
+        }
+        const int going = __syncthreads_or(more);
+        const int queued = min(qn, qend);
+        float x[3], y[3];
+        auto fetch = [&](int e, float *v) {
+            if (e >= queued) return;
+            const float *s = pos + 3 * (size_t)qp[e];
+            v[0] = s[0];
+            v[1] = s[1];
+            v[2] = s[2];
+        };
+        fetch(tid, x);
+        for (int e = tid; e < queued; e += GTPB) {
+            fetch(e + GTPB, y);   // the next particle's, while this one is added
+            deposit(x, ql[e]);
+            x[0] = y[0];
+            x[1] = y[1];
+            x[2] = y[2];
+        }
+        __syncthreads();
+        if (going == 0) break;
+        if (tid == 0) {
+            qn = 0;
+            qend = KQ;
+        }
+        __syncthreads();
+    }
+    for (int q = tid; q < CG_CELLS; q += GTPB) {
         const int tx = q % CGX, ty = (q / CGX) % CGY, tz = q / (CGX * CGY);
         const size_t t = ((size_t)(z0 + tz) << (2 * logn)) + ((size_t)(y0 + ty) << logn) + (x0 + tx);
-        delta[t] = (T)((double)acc[q] * scale - 1.0);
+        delta[t] = (T)((double)acc[((tz + 1) * CPY + ty + 1) * CPX + tx + 1] * scale - 1.0);
     }
 }
 
@@ -349,7 +371,7 @@ mg_status cic(int n_mesh, int n_part, const float *pos, T *delta, unsigned long 
         int *next = head + ncell;
         k_fill_i32<<<nb(ncell), PTPB, 0, s>>>(head, ncell, -1);
         k_cic_link<<<nb(np), PTPB, 0, s>>>(pos, (int)np, logn, head, next);
-        k_cic_gather<T><<<(unsigned)(ncell / CG_CELLS), PTPB, 0, s>>>(pos, logn, head, next,
+        k_cic_gather<T><<<(unsigned)(ncell / CG_CELLS), GTPB, 0, s>>>(pos, logn, head, next,
                                                                      scale, delta);
         return hip_status(s, false);
     }
