@@ -315,16 +315,17 @@ TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2, int blocks
 }
 
 // z-planes per block of the sweep kernel, whose chunks re-read four planes and
-// recompute two: the deepest chunk (4 .. 128 planes) that gives the launch two
+// recompute two: the deepest chunk (4 .. 256 planes) that gives the launch two
 // blocks per CU, 512, which is also what is resident.  512^3 solve with at
-// most 32, 64 and 128 planes: 33.9, 33.4 and 32.9 ms; 256^3 with 512 blocks
-// (32 planes) 5.89 ms, with 1024 6.06 ms, with 256 6.38 ms.
+// most 32, 64, 128 and 256 planes: 30.6, 29.6, 29.4 and 28.95 ms; 1024^3 PM
+// step with 64, 128, 256 and 512: 163, 168, 161 and 164 ms; 256^3 with 512
+// blocks (32 planes) 5.89 ms, with 1024 6.06 ms, with 256 6.38 ms.
 TileGeom sweep_geom(int n) {
     TileGeom G;
     G.ntx = (n / 2) / TX;
     G.nty = n / TY;
     const long per = (long)G.ntx * G.nty;
-    int kz = 128;
+    int kz = 256;
     while (kz > 4 && n / kz * per < 512) kz >>= 1;
     G.kz = kz;
     return G;
