@@ -271,17 +271,13 @@ int ilog2i(int n) {
     return l;
 }
 
-// line pairs per block: about 256 threads (x) or 512 (y, z: 16 lines, a
-// 128-byte row segment, at n = 1024), at most n / 2
-#ifndef MG_FFT_THREADS_X
-#define MG_FFT_THREADS_X 256
-#endif
-#ifndef MG_FFT_THREADS_YZ
-#define MG_FFT_THREADS_YZ 512
-#endif
-#ifndef MG_FFT_THREADS_Z
-#define MG_FFT_THREADS_Z MG_FFT_THREADS_YZ
-#endif
+// line pairs per block: 256 threads along x; along y and z 512 threads from
+// n = 512 (rows of 16 lines at n = 1024, a 128-byte segment), where the length of
+// the segments counts, and 256 below, where the number of blocks does.  Whole
+// solve with 256 and 512 threads: 128^3 63 and 71 us, 256^3 253 and 283 us,
+// 512^3 2.48 and 2.39 ms, 1024^3 26.7 and 22.4 ms.
+constexpr int threads_x = 256;
+constexpr int threads_yz(int logn) { return logn <= 8 ? 256 : 512; }
 constexpr int pairs_per_block(int logn, int threads) {
     const int n = 1 << logn, r0 = logn < 4 ? (1 << logn) : 16;
     const int np = threads * r0 / n;
@@ -317,15 +313,14 @@ template <int LOGN>
 mg_status poisson_passes(const double *delta, double *phi, const double2 *w, double scale,
                          hipStream_t stream) {
     constexpr int n = 1 << LOGN;
-    constexpr int NPX = pairs_per_block(LOGN, MG_FFT_THREADS_X);
-    constexpr int NPYZ = pairs_per_block(LOGN, MG_FFT_THREADS_YZ);
-    constexpr int NPZ = pairs_per_block(LOGN, MG_FFT_THREADS_Z);
+    constexpr int NPX = pairs_per_block(LOGN, threads_x);
+    constexpr int NPYZ = pairs_per_block(LOGN, threads_yz(LOGN));
     const size_t nn = (size_t)n * n;
     const PassGeo GX{nn, 1, (size_t)n, 0}, GY{nn, (size_t)n, 1, 0}, GZ{(size_t)n, nn, 1, 1};
     mg_status rc;
     if ((rc = launch_pass<LOGN, NPX, true, false>(delta, phi, GX, w, 0.0, stream)) != MG_OK) return rc;
     if ((rc = launch_pass<LOGN, NPYZ, false, false>(phi, phi, GY, w, 0.0, stream)) != MG_OK) return rc;
-    if ((rc = launch_pass<LOGN, NPZ, false, true>(phi, phi, GZ, w, scale, stream)) != MG_OK) return rc;
+    if ((rc = launch_pass<LOGN, NPYZ, false, true>(phi, phi, GZ, w, scale, stream)) != MG_OK) return rc;
     if ((rc = launch_pass<LOGN, NPYZ, false, false>(phi, phi, GY, w, 0.0, stream)) != MG_OK) return rc;
     return launch_pass<LOGN, NPX, true, false>(phi, phi, GX, w, 0.0, stream);
 }
