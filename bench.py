@@ -74,11 +74,14 @@ def vcycle_bytes(n: int, fused: bool = False) -> int:
     plus the coarse FAS source (40 B per coarse cell).  fused: the bytes the
     executed kernels must move, where levels >= 128^3 run both colours of a
     sweep in one launch (24 B/cell instead of 32) and the prolongation with
-    the first post-smoothing sweep (26 instead of 18 + 32)."""
+    the first post-smoothing sweep (26 instead of 18 + 32), and form a coarse
+    level's source in its first sweep (40 instead of 40 + 24)."""
     total, m, lev = 0, n, 0
     while m > 4:
         per = 68 if (fused and m >= 128) else 100
-        total += per * m ** 3 + (40 * m ** 3 if lev else 0)
+        if lev:
+            per += 16 if (fused and m >= 128) else 40
+        total += per * m ** 3
         m //= 2
         lev += 1
     return total

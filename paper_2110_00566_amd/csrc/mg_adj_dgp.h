@@ -26,12 +26,11 @@
 // of plane kp - 2, which completes the target cells of plane kp - 3.
 // Per cell and colour pass 28 B: mu of both colours, phi of the target
 // colour, F' of both colours, f and the new value.
-// At 512^3 a colour pass takes 785 us (4.8 TB/s of those 28 B) and a residual
-// + restriction 821 us; forming each product where it is staged, with phi
-// read from a ring of 12 x 68 planes and two barriers a plane, they took 1150
-// and 1193 us.  84 to 104 VGPRs: two blocks a CU; what is left over a copy of
-// the same bytes is the 1.5 row and 1.03 column halo of the phi planes and the
-// LDS traffic of 11 reads and 5 writes a column and plane.
+// At 512^3 a colour pass takes 747 us (5.0 TB/s of those 28 B, 6.0 with the
+// halo: HBM bounds it) and a residual + restriction 796 us; forming each
+// product where it is staged, with phi read from a ring of 12 x 68 planes and
+// two barriers a plane, they took 1150 and 1193 us.  84 to 104 VGPRs: two
+// blocks a CU; 11 LDS reads and 5 writes a column and plane.
 #pragma once
 #include "mg_adj_tiled.h"
 #include "mg_sweep.h"

@@ -292,16 +292,15 @@ bool tiled_level(int n) { return n >= 128; }
 // The tiled kernels implement the closed-form update only.
 constexpr bool tiled_op(int OP) { return OP != OP_ADJ; }
 
-// z-planes per block: the deepest chunk (2 .. kzmax planes) that still gives
-// a launch at least 2048 blocks.  Deeper chunks re-read fewer z-halo planes;
-// fewer blocks leave a level of 128^3 latency-bound (its residual +
-// restriction took 24 us with 256 blocks, 18 us with 512, its coarse source
-// 22 and 18.6 us with 512 and 1024).  512^3: 4096, 2048 and 1024 blocks give
-// 555, 560 and 571 us for the residual + restriction, 123, 117 and 118 us for
-// the 256^3 coarse source.  Kernels whose chunks count coarse planes (two fine
-// planes each) keep at most 64: the 1024^3 residual + restriction took 4.43 ms
-// with 128 against 4.31 ms with 64.  The adjoint kernels, which stage four planes
-// before the first result, keep at least 4 (128^3 gradient 8.6 ms, 8.9 with 2).
+// z-planes per block of the kernels of mg_tiled.h, mg_dc.h and mg_adj_tiled.h:
+// the deepest chunk (2 .. kzmax planes) that still gives a launch at least
+// 2048 blocks.  Deeper chunks re-read fewer z-halo planes; fewer blocks leave
+// a level of 128^3 latency-bound (its coarse source took 22 us with 512 blocks,
+// 18.6 us with 1024).  The 256^3 coarse source takes 123, 117 and 118 us with
+// 4096, 2048 and 1024 blocks.  Kernels whose chunks count coarse planes (two
+// fine planes each) keep at most 64.  The adjoint kernels, which stage four
+// planes before the first result, keep at least 4 (128^3 gradient 8.6 ms, 8.9
+// with 2).
 TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2, int blocks = 2048) {
     TileGeom G;
     G.ntx = (n / 2) / TX;

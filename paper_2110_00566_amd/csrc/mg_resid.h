@@ -17,10 +17,9 @@
 // wave of the row below, which adds the eight children of a coarse cell in
 // the order of k_resid_restrict and stores it one step later.
 //
-// 512^3 FP64: 508 to 530 us, 4.6 to 4.8 TB/s of its 18 B per cell (560 us with
-// three staged planes, two barriers a plane and 38 LDS reads for two cells);
-// FP32 380 us, 3.5 TB/s (405 us), bound by instruction issue; 256^3 Kmouflage 88
-// -> 70 us.
+// 512^3 FP64: 495 us, 4.9 TB/s of its 18 B per cell (560 us with three staged
+// planes, two barriers a plane and 38 LDS reads for two cells); FP32 355 to 380
+// us, 3.3 TB/s (405 us), bound by instruction issue; 256^3 Kmouflage 88 -> 70 us.
 #pragma once
 #include "mg_sweep.h"
 

@@ -26,10 +26,10 @@
 // plane kp - 1 and the colour-1 cells of plane kp - 3, writes the staged
 // values of plane kp + 1 and starts the loads of plane kp + 2.
 //
-// At 512^3 FP64 a sweep takes 610 us, 5.3 TB/s of its 24 B per cell (830 us as
-// two colour passes): HBM bounds it.  FP32, 410 us, is bound by instruction
+// At 512^3 FP64 a sweep takes 600 us, 5.4 TB/s of its 24 B per cell (830 us as
+// two colour passes): HBM bounds it.  FP32, 400 us, is bound by instruction
 // issue: its vector instructions fill 80% of the cycles.  The prolongation adds
-// 115 us (190 us before a coarse plane's in-plane part was kept for the fine
+// 115 us (210 us before a coarse plane's in-plane part was kept for the fine
 // planes that it serves).  Registers are what two blocks per CU leave short (128
 // a thread, 100 to 128 used): see the opaque copies and pins below.
 #pragma once
