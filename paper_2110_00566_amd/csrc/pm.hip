@@ -157,8 +157,8 @@ __global__ __launch_bounds__(GTPB) void k_cic_gather(const float *__restrict__ p
         qend = KQ;
     }
     __syncthreads();
-    // 2^32 w <= 2^32, rounded to an integer by the addition of 2^52, whose bits
-    // are then taken off
+    // 0 <= 2^32 w <= 2^32, rounded to an integer by the addition of 2^52, whose
+    // bits are then taken off
     auto fixed = [](double w) {
         const double v = fma(w, FIX_SCALE, 0x1p52);
         return (unsigned long long)(unsigned)(__double2hiint(v) - 0x43300000) << 32 |
@@ -168,6 +168,9 @@ __global__ __launch_bounds__(GTPB) void k_cic_gather(const float *__restrict__ p
         double f[3];
         int i0[3];
         cic_weights(x, f, i0);
+        // a position that is not finite makes all eight weights NaN, which the
+        // scatter form's conversion rounds to 0
+        if (!(f[0] + f[1] + f[2] < 4.0)) return;
 #pragma unroll
         for (int o = 0; o < 8; ++o) {
             const int a = o & 1, b = (o >> 1) & 1, c = o >> 2;
