@@ -462,6 +462,13 @@ bool setup_dgp(const mg_dgp_params *p, Mod &M) {
     M.alpha = 3.0 * beta * p->a * p->a / (p->h0rc * p->h0rc);
     M.sgn = M.alpha >= 0.0 ? 1.0 : -1.0;
     M.s = M.alpha / beta * om / p->a;
+    // FP32 terms keep alpha^2 far above the least root of sqrt_normal (1e-28)
+    // and out of the subnormal numbers: alpha fscale in [2^-31, 2^-30), by at
+    // most 2^60 (FP32 has no more room for the products)
+    if (M.alpha < 0x1p-30) {
+        M.fscale = std::ldexp(1.0, std::min(60, -30 - (std::ilogb(M.alpha) + 1)));
+        M.fback = 2.0 / M.fscale;
+    }
     return true;
 }
 

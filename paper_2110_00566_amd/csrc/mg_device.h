@@ -26,6 +26,7 @@ enum { MODEL_DGP = 0, MODEL_KMO = 1, MODEL_POISSON = 2 };
 // Level-independent model coefficients (host-computed).
 struct Mod {
     double alpha, sgn, s;     // nDGP: alpha = 3 beta a^2 / R_c^2, s = alpha Omega_m/(beta a)
+    double fscale = 1.0, fback = 2.0;   // nDGP in FP32: see model_term; 2 / fscale
     double ctil, src;         // Kmouflage: c~, 3 beta A(phibar) Omega_m / a
     double c0;                // 1 + gamma (phibar'/H0)^(2(n-1))
     double a1;                // (2n+1) gamma / 3
@@ -157,10 +158,12 @@ __device__ __forceinline__ T dgp_sigma_over_alpha(const Mod &M, const L_ &L, con
     return dgp_sigma_over_alpha<T>(M, L, comb(s), delta);
 }
 
-// Square root of a positive x that needs no scaling (x > 2^-767): the Newton
-// iterations on the hardware's reciprocal root estimate that sqrt() runs,
-// with its result, without the scaling and special-case instructions around
-// them.  NaN stays NaN; infinity gives NaN.
+// Square root of a positive normal x: Goldschmidt's iteration (P. Markstein,
+// "Software division and square root using Goldschmidt's algorithms", RNC 6,
+// 2004) from the hardware's estimate of the reciprocal root, without the scaling
+// of small x and the special cases.  Rounded as sqrt() rounds for x >= 2^-767;
+// below, where the remainders lose bits, within one unit in the last place.
+// NaN stays NaN; infinity gives NaN.
 __device__ __forceinline__ double sqrt_normal(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
@@ -170,7 +173,7 @@ __device__ __forceinline__ double sqrt_normal(double x) {
     g = fma(fma(-g, g, x), h, g);
     return fma(fma(-g, g, x), h, g);
 }
-// The same in FP32 (x > 2^-96), rounded as sqrtf() rounds.
+// The same in FP32; rounded as sqrtf() rounds for x >= 2^-96.
 __device__ __forceinline__ float sqrt_normal(float x) {
     const float y = __builtin_amdgcn_rsqf(x);
     float g = x * y, h = 0.5f * y;
@@ -219,17 +222,21 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
             // (equal to the printed one; accurate relative to K when
             // Sigma << alpha^2).  A clamped D gives -3 alpha / 4 as above.
             // The products are fused explicitly, so that every kernel rounds
-            // the term alike.
+            // the term alike.  D and alpha are formed times fscale^2 and fscale,
+            // a power of two: 1 unless alpha < 2^-30.
+            const double f2 = M.fscale * M.fscale;
+            const float af = (float)(M.fscale * M.alpha);
             const float u3 = fmaf(dyz, dyz, fmaf(dxy, dxy, dxz * dxz));
             const float u8 = fmaf(s.nyz, s.nyz, fmaf(s.nxy, s.nxy, s.nxz * s.nxz));
-            const float sig = fmaf((float)M.s, delta,
-                                   fmaf(u3, (float)L.c3h4, u8 * (float)L.c8h4));
-            const float disc = fmaf(8.0f / 3.0f, sig, (float)(M.alpha * M.alpha));
+            const float sig = fmaf((float)(f2 * M.s), delta,
+                                   fmaf(u3, (float)(f2 * L.c3h4), u8 * (float)(f2 * L.c8h4)));
+            const float disc = fmaf(8.0f / 3.0f, sig, (float)(f2 * (M.alpha * M.alpha)));
             const bool neg = disc < 0.0f;
             if (neg) count_clamp(clamp);
-            // root 1e-14 at least: nothing beside alpha
+            // root 1e-14 at least: nothing beside alpha, which is 2^-31 or more here
             const float root = sqrt_normal(disc < 1e-28f ? 1e-28f : disc);
-            const float K = div_normal(2.0f * sig, fmaf((float)M.sgn, root, (float)M.alpha));
+            const float K = div_normal((float)M.fback * sig,
+                                       fmaf((float)M.sgn, root, af));
             return neg ? (T)(-0.75 * M.alpha) : K;
         }
         const T t3 = dxy * dxy + dxz * dxz + dyz * dyz;
@@ -237,7 +244,9 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
         const double sig = (double)t3 * L.c3h4 + (double)t8 * L.c8h4 + M.s * (double)delta;
         double disc = M.alpha * M.alpha + (8.0 / 3.0) * sig;
         if (disc < 0.0) count_clamp(clamp);
-        disc = disc < 1e-280 ? 1e-280 : disc;   // root 1e-140: nothing beside alpha
+        // any normal number: root 1.5e-154 at least, beside which only an alpha^2
+        // that underflows is small
+        disc = disc < 0x1p-1022 ? 0x1p-1022 : disc;
         return (T)(0.75 * (M.sgn * sqrt_normal(disc) - M.alpha));
     }
     // Kmouflage split form eq:kmf_eqn_codeunit_final: with e = 2h grad phi,
