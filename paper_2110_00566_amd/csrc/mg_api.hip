@@ -492,6 +492,11 @@ bool setup_kmo(const mg_kmo_params *p, int n, Mod &M) {
     M.b2 = -2.0 * M.ctil * (p->n_k - 1) * gamma;
     M.src = 3.0 * p->beta * std::exp(p->beta * p->phibar) * p->omega_m / p->a;
     M.nk = p->n_k;
+    // qctil in [2^-40, 2^-39) for c~ < 1, as c0 >= 1 keeps the divisor above it
+    const int e = -40 - std::min(0, std::ilogb(M.ctil));
+    M.qctil = std::ldexp(M.ctil, e);
+    M.qsrc = std::ldexp(M.src, e);
+    M.qb2 = std::ldexp(M.b2, e);
     return true;
 }
 
