@@ -235,7 +235,7 @@ mg_status mg_solve_dgp(const mg_opts *opts, const mg_dgp_params *par, const void
 
 /* mg_solve_dgp for callers that cannot allocate (serving loops, harnesses
  * that forbid allocation): same solve, same kernels, same arguments minus the
- * workspace.  The workspace is a static device array of 90 MiB inside the
+ * workspace.  The workspace is a static device array of 106 MiB inside the
  * library, one per GPU (the current device's), created when the library's
  * code is loaded on that GPU and held until the process ends.  Limit:
  * opts->n <= 128 in every precision (larger meshes: MG_ERR_ARG; use

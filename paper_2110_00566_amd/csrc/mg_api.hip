@@ -1548,9 +1548,9 @@ mg_status common_checks(const mg_opts *o, const void *delta, const void *phi, vo
 }
 
 // Workspace of mg_solve_dgp_noalloc: enough for any precision at n <= 128
-// (mg_workspace_bytes(128, MG_MIXED, MG_MODEL_DGP, 0) is 89.3 MiB).
+// (mg_workspace_bytes(128, MG_MIXED_DC, MG_MODEL_DGP, 0) is 105.24 MiB).
 constexpr int NOALLOC_MAX_N = 128;
-constexpr size_t NOALLOC_BYTES = (size_t)90 << 20;
+constexpr size_t NOALLOC_BYTES = (size_t)106 << 20;
 
 }  // namespace
 
@@ -1642,7 +1642,7 @@ mg_status mg_solve_dgp_noalloc(const mg_opts *opts, const mg_dgp_params *par,
     if (rc != MG_OK) return rc;
     if (opts->n > NOALLOC_MAX_N)
         return fail(MG_ERR_ARG, "mg_solve_dgp_noalloc: opts.n must be <= 128 (its static "
-                                "workspace holds 90 MiB); use mg_solve_dgp for larger meshes");
+                                "workspace holds 106 MiB); use mg_solve_dgp for larger meshes");
     if (opts->profile) return fail(MG_ERR_ARG, "mg_solve_dgp_noalloc: profile must be 0");
     if (!delta || !phi) return fail(MG_ERR_ARG, "delta and phi must be device pointers");
     if (!stats) return fail(MG_ERR_ARG, "stats is NULL");
