@@ -24,7 +24,9 @@
  *    start on a 256-byte boundary (hipMalloc's and torch's allocations do).
  *  - Solver calls read the stopping residual through one 128-byte pinned
  *    host buffer per calling thread, allocated on first use and kept until
- *    the process ends.
+ *    the process ends.  The thread spins while it waits for a residual, as the
+ *    HIP runtime does by default; with hipDeviceScheduleBlockingSync or
+ *    hipDeviceScheduleYield set on the device it waits through the runtime.
  */
 #ifndef MGGLAM_H
 #define MGGLAM_H
