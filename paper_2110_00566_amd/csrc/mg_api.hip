@@ -556,6 +556,8 @@ struct PhaseResult {
 
 template <int OP, typename R>
 struct Solver {
+    static_assert(sizeof(R) == 8 || (OP != OP_ADJ && OP != OP_NEWTON),
+                  "the adjoint and the Newton comparator are FP64 only");
     Ctx &C;
     Hier<R> &Hh;
     explicit Solver(Ctx &c) : C(c), Hh(hier<R>(c)) {}
@@ -1224,7 +1226,8 @@ template <int OP>
 mg_status dc_finish(const mg_opts *o, Ctx &C, DeltaIn delta, double *phi, mg_stats *st,
                     const PhaseResult &p32, int cycles32,
                     std::chrono::steady_clock::time_point t0) {
-    constexpr int MODEL = OP == OP_POISSON ? MODEL_POISSON : MODEL_DGP;
+    static_assert(OP == OP_DGP || OP == OP_POISSON, "corr_term covers nDGP and Poisson");
+    constexpr int MODEL = OP;
     HLevel<double> &F = C.h64.lv[0], &Hc = C.h64.lv[1];
     HLevel<float> &G = C.h32.lv[0];
     const double ncell = (double)F.n * F.n * F.n;
@@ -1338,11 +1341,15 @@ mg_status forward_solve(const mg_opts *o, const Mod &M, const void *delta_p, dou
     Profiler prof(C, o->profile != 0 && !noalloc, 2 * (o->nu_pre + o->nu_post) + 2);
     if (!noalloc && !C.no_sync) arm_host_scalars(C);
     reset_scalars(C);
-    if (o->precision == MG_FP32) return fp32_solve<OP>(o, C, delta, phi, st, t0);
     HLevel<double> &F = C.h64.lv[0];
     PhaseResult p32, p64;
     int cycles32 = 0;
-    if (mixed) {
+    if constexpr (OP == OP_NEWTON) {   // FP64 only (checked by the caller)
+        k_pack<double, double><<<nblocks(2 * F.half), TPB, 0, C.st>>>(phi, F.logn, F.u[0],
+                                                                      F.u[1], nullptr);
+    } else if (o->precision == MG_FP32) {
+        return fp32_solve<OP>(o, C, delta, phi, st, t0);
+    } else if (mixed) {
         // FP32-storage cycles until the residual stops falling (FP32 floor)
         density_hierarchy<float>(C, delta);
         HLevel<float> &G = C.h32.lv[0];
@@ -1359,7 +1366,9 @@ mg_status forward_solve(const mg_opts *o, const Mod &M, const void *delta_p, dou
         cycles32 = p32.cycles;
         st->cycles_fp32 = cycles32;
         st->eps_fp32 = p32.eps;
-        if (dc) return dc_finish<OP>(o, C, delta, phi, st, p32, cycles32, t0);
+        if constexpr (OP == OP_DGP || OP == OP_POISSON) {
+            if (dc) return dc_finish<OP>(o, C, delta, phi, st, p32, cycles32, t0);
+        }
         k_convert<float, double><<<nblocks(G.half), TPB, 0, C.st>>>(G.u[0], F.u[0], G.half);
         k_convert<float, double><<<nblocks(G.half), TPB, 0, C.st>>>(G.u[1], F.u[1], G.half);
     } else {
