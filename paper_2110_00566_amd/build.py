@@ -1,4 +1,5 @@
-"""Build libmgglam.so (gfx950) in-tree with hipcc.
+"""Build libmgglam.so (gfx950) in-tree with hipcc, and the small library of
+tests/rounding that the tests of the rounding of the model terms load.
 
     python -m paper_2110_00566_amd.build
 
@@ -17,6 +18,8 @@ LIB = os.path.join(HERE, "libmgglam.so")
 SOURCES = ["mg_api.hip", "pm.hip", "fft.hip", "kmo_background.cpp"]
 HEADERS = ["mg_device.h", "mg_kernels.h", "mg_tiled.h", "mg_adjoint.h", "mg_adj_tiled.h",
            "mg_adj_dgp.h", "mg_dc.h", "mg_sweep.h", "mg_resid.h", "mg_small.h"]
+ROUNDING = os.path.join(os.path.dirname(HERE), "tests", "rounding")
+ROUNDING_LIB = os.path.join(ROUNDING, "librounding.so")
 ARCH = os.environ.get("MGGLAM_ARCH", "gfx950")
 
 
@@ -27,16 +30,22 @@ def hipcc() -> str:
     return "hipcc"
 
 
-def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp%d" % os.getpid()
+def compile_lib(lib: str, sources: list[str], verbose: bool) -> str:
+    tmp = lib + ".tmp%d" % os.getpid()
     cmd = [hipcc(), "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wall", "-Wno-unused-result", "-o", tmp] + [os.path.join(CSRC, s) for s in SOURCES]
+           "-Wall", "-Wno-unused-result", "-o", tmp] + sources
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, lib)
+    return lib
+
+
+def build(verbose: bool = False) -> str:
+    if os.path.isdir(ROUNDING):
+        compile_lib(ROUNDING_LIB, [os.path.join(ROUNDING, "rounding.hip")], verbose)
+    return compile_lib(LIB, [os.path.join(CSRC, s) for s in SOURCES], verbose)
 
 
 if __name__ == "__main__":
