@@ -513,7 +513,8 @@ bool setup_kmo(const mg_kmo_params *p, int n, Mod &M) {
     M.src = 3.0 * p->beta * std::exp(p->beta * p->phibar) * p->omega_m / p->a;
     M.nk = p->n_k;
     // qctil in [2^-40, 2^-39) for c~ < 1, as c0 >= 1 keeps the divisor above it
-    const int e = -40 - std::min(0, std::ilogb(M.ctil));
+    const int e = -40 - std::max(-1000, std::min(0, std::ilogb(M.ctil)));
+    M.q = std::ldexp(1.0, e);
     M.qctil = std::ldexp(M.ctil, e);
     M.qsrc = std::ldexp(M.src, e);
     M.qb2 = std::ldexp(M.b2, e);

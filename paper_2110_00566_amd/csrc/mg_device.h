@@ -28,7 +28,7 @@ struct Mod {
     double alpha, sgn, s;     // nDGP: alpha = 3 beta a^2 / R_c^2, s = alpha Omega_m/(beta a)
     double fscale = 1.0, fback = 2.0;   // nDGP in FP32: see model_term; 2 / fscale
     double ctil, src;         // Kmouflage: c~, 3 beta A(phibar) Omega_m / a
-    double qctil, qsrc, qb2;  // c~, src and b2 times one power of two, see model_term
+    double q, qctil, qsrc, qb2;   // a power of two; c~, src and b2 times it, see model_term
     double c0;                // 1 + gamma (phibar'/H0)^(2(n-1))
     double a1;                // (2n+1) gamma / 3
     double b2;                // -2 c~ (n-1) gamma
@@ -256,10 +256,11 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
     //   g = |e|^2/(4h^2),  Q = hat(H)_ij G_i G_j
     //     = [e_x^2 (2A_x-A_y-A_z) + ...]/(12 h^4) + (N_xy e_x e_y + ...)/(8 h^4),
     //   K = (src delta + b2 g^(n-2) Q) / (c~ (c0 + a1 g^(n-1))).
-    // Both parts are formed times a power of two (2^-40 for c~ >= 1), which
-    // leaves the quotient as it is and lets g^(n-1) rise 2^40 higher; beyond, the
-    // divisor stays at the last value with a normal reciprocal (K is then next
-    // to 0) instead of turning infinite, of which div_normal makes a NaN.
+    // The divisor is formed times a power of two (2^-40 for c~ >= 1), which lets
+    // g^(n-1) rise 2^40 higher.  The dividend takes the same factor in FP64; in
+    // FP32, where a small delta would lose bits, the quotient does.  Beyond, the
+    // divisor stays at the last value with a normal reciprocal (K is then next to
+    // 0) instead of turning infinite, of which div_normal makes a NaN.
     const T ex = s.ex, ey = s.ey, ez = s.ez;
     if constexpr (sizeof(T) == 4) {
         // FP32 storage: the whole term in FP32 (its relative error stays far
@@ -274,8 +275,8 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
         float gn2 = 1.0f;
         for (int t = 0; t < M.nk - 2; ++t) gn2 *= g;
         const float sig1 = fmaf(g, gn2 * (float)M.a1, (float)M.c0);
-        return div_normal(fmaf(delta, (float)M.qsrc, q * (gn2 * (float)M.qb2)),
-                          fminf((float)M.qctil * sig1, 0x1p126f));
+        return (float)M.q * div_normal(fmaf(delta, (float)M.src, q * (gn2 * (float)M.b2)),
+                                       fminf((float)M.qctil * sig1, 0x1p126f));
     }
     const double g = (double)(ex * ex + ey * ey + ez * ez) * L.c4h2;
     const double q = (double)(ex * ex * (2 * ax - ay - az) + ey * ey * (2 * ay - ax - az)
@@ -285,7 +286,9 @@ __device__ __forceinline__ T model_term(const Mod &M, const L_ &L, const CombT<T
     for (int t = 0; t < M.nk - 2; ++t) gn2 *= g;
     const double sig1 = M.c0 + M.a1 * gn2 * g;
     const double sig2 = M.qb2 * gn2 * q;
-    return (T)div_normal(M.qsrc * (double)delta + sig2, fmin(M.qctil * sig1, 0x1p1022));
+    const double b = M.qctil * sig1;   // > 0: held below 2^1021 (1 + 2^-20) by its upper word
+    return (T)div_normal(M.qsrc * (double)delta + sig2,
+                         __hiloint2double(min(__double2hiint(b), 0x7fc00000), __double2loint(b)));
 }
 
 template <int MODEL, typename T, typename L_, typename Clamp>

@@ -32,6 +32,16 @@ import paper_2110_00566_amd as mg
 pytestmark = pytest.mark.gpu
 
 
+def test_fp32_kmouflage_with_a_small_density():
+    # delta = 1e-30: the term is linear there, and every factor of the FP32 sums
+    # stays a normal number; reference: the FP64 field
+    d = delta_of(32) * 1e-30
+    kw = dict(box_mpch=32.0, n_k=3, beta=0.2, tol=0.0, max_cycles=12)
+    ref, _ = mg.solve_kmouflage(d, **kw)
+    phi, _ = mg.solve_kmouflage(d, precision=mg.MG_FP32, **kw)
+    assert float((phi - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+
+
 def delta_of(n):
     return torch.from_numpy(inputs.lognormal_delta(n, 11)).to("cuda")
 
