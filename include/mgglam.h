@@ -100,7 +100,10 @@ typedef struct {
     int cycle;        /* mg_cycle: MG_CYCLE_V (default), MG_CYCLE_F or MG_CYCLE_W;
                          mg_solve_adjoint accepts MG_CYCLE_V only */
     int profile;      /* 1: time the finest-level smoothing with HIP events
-                         on the caller's stream (stats.pass_ms_avg) */
+                         on the caller's stream (stats.pass_ms_avg).  Meshes up to
+                         64^3 then run the finest level's passes, residual and
+                         prolongation in launches of their own instead of the fused
+                         ones (the same up to rounding, 2-3 times the time) */
     int delta_fp32;   /* 0: the solves' delta is FP64 (double *); 1: FP32 (float *),
                          any precision (it is widened or kept as the levels store
                          it; half the bytes of the caller's array).  phi and every

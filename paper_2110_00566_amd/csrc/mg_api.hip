@@ -316,11 +316,12 @@ constexpr bool tiled_op(int OP) { return OP != OP_ADJ; }
 // the deepest chunk (2 .. kzmax planes) that still gives a launch at least
 // 2048 blocks.  Deeper chunks re-read fewer z-halo planes; fewer blocks leave
 // a level of 128^3 latency-bound (its coarse source took 22 us with 512 blocks,
-// 18.6 us with 1024).  The 256^3 coarse source takes 123, 117 and 118 us with
-// 4096, 2048 and 1024 blocks.  Kernels whose chunks count coarse planes (two
-// fine planes each) keep at most 64.  The adjoint kernels, which stage four
-// planes before the first result, keep at least 4 (128^3 gradient 8.6 ms, 8.9
-// with 2).
+// 18.6 us with 1024).  256^3 Kmouflage gradient with 4096, 2048 and 1024 blocks:
+// 20.3, 18.6 and 17.8 ms (Poisson 6.06, 5.69, 5.71); 256^3 solve with defect
+// correction, eight cycles: 2.95, 2.92 and 2.92 ms; 512^3: 18.9 ms with each, 19.0
+// with 1024.  Kernels whose chunks count coarse planes (two fine planes each)
+// keep at most 64.  The adjoint kernels, which stage four planes before the first
+// result, keep at least 4 (128^3 Kmouflage gradient 3.21 ms, 3.63 with 2).
 TileGeom tile_geom(int n, int planes, int kzmax = 128, int kzmin = 2, int blocks = 2048) {
     TileGeom G;
     G.ntx = (n / 2) / TX;

@@ -10,11 +10,11 @@
 // consecutive packed x positions, so every load and store is coalesced.
 //
 // Precision: the storage type R is double (FP64 solve) or float (the FP32
-// phase of the mixed solve).  With float storage the nDGP colour pass runs in
-// float, with the closed-form root in its cancellation-free form (the
-// Kmouflage term keeps its sums and division in double); the residual
-// evaluates the Laplacian in double from the float values and the nDGP term
-// in float; restriction sums and reductions are always evaluated in double.
+// phase of the mixed solve).  With float storage the colour passes run in
+// float, the nDGP root in its cancellation-free form; the residual evaluates
+// the Laplacian in double from the float values, and the model term in float on
+// levels of 128^3 and more, in double below; coarse sources, restriction sums and
+// reductions are always evaluated in double.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

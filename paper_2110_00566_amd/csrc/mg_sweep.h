@@ -31,7 +31,8 @@
 // issue: its vector instructions fill 80% of the cycles.  The prolongation adds
 // 115 us (210 us before a coarse plane's in-plane part was kept for the fine
 // planes that it serves).  Registers are what two blocks per CU leave short (128
-// a thread, 100 to 128 used): see the opaque copies and pins below.
+// a thread): nDGP uses 98 to 127, Kmouflage 113 to 128 (its prolongation sweep of a
+// coarse level spills one, 8 bytes a thread): see the opaque copies and pins below.
 #pragma once
 #include <type_traits>
 #include "mg_tiled.h"
@@ -264,8 +265,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tiled(Mod M, LvlT<R> L, R *
     __shared__ R sC[2][TPLANE];   // new colour-0 values, rows -1 .. TY
     // the coarse correction; CARRY: its in-plane part is kept in registers and
     // one coarse plane is staged; FP64 Kmouflage and Newton have none to spare
-    // (Kmouflage spills, 125 -> 158 us at 256^3) and form it for every fine
-    // plane from a ring of coarse planes
+    // (carried, Kmouflage spills 60 bytes a thread: 125 -> 158 us at 256^3) and
+    // form it for every fine plane from a ring of coarse planes
     constexpr bool CARRY = OP == OP_DGP || OP == OP_POISSON || sizeof(R) == 4;
     __shared__ R sE[PROLONG && !CARRY ? 4 : 1][PROLONG ? SCPLANE : 1];
     const size_t blk = xcd_block(blockIdx.x, gridDim.x);
